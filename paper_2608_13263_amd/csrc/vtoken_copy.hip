@@ -29,22 +29,31 @@ __device__ __forceinline__ int lanes_below(uint64_t mask) {
 // ------------------------------------------------------------------------------------------
 // Step 2: the gather-repack. Destination block g of a plane is one contiguous chunk of
 // S*row_bytes bytes at block free_list[g], whose row j comes from the source slot
-// src_plan[g*S + j]. A work item is (part of destination block g, plane), a part being one
-// round of kCopyThreads*kV 16-byte units (32 KiB at kV = 8): every workgroup moves one round
-// whatever the block size, and a chunk of several rounds (S = 32 or 48 at 2 KiB rows) is
-// spread over several workgroups. A thread loads its kV units before storing any, so every
-// wave keeps kV*1 KiB of reads in flight. Rows are head_dim-contiguous, so a wave's 64 lanes
-// read and write 1 KiB of consecutive bytes per instruction (a whole 2 KiB row takes two).
+// src_plan[g*S + j]. A piece is (part of destination block g, plane), a part being one round of
+// kU 16-byte units per thread (32 KiB at kU = 8): a chunk of several rounds (S = 32 or 48 at
+// 2 KiB rows) is several pieces, and a chunk of at most 128 (64) units takes only two waves (one
+// wave) of the workgroup, which then moves two (four) pieces side by side. Rows are
+// head_dim-contiguous, so a wave's 64 lanes read and write 1 KiB of consecutive bytes per
+// instruction (a whole 2 KiB row takes two).
+//
+// Bound: HBM, where a piece's loads are in flight early enough. A piece is a chain of dependent
+// reads (counters, then destination block and plan entries, then rows) and then its stores, so
+// a workgroup that takes one small piece and ends is bound by that chain: 434K pieces of 4 KiB
+// (fp8, 80 layers, 2 heads x 64, S = 32) took 1.53 ms that way, 2.3 TB/s. Every workgroup
+// therefore walks pieces with two of them in flight: the next piece's loads are issued before
+// this one's stores, and the plan entries of the one after that before either (that call: 0.59
+// ms, 5.9 TB/s; 2 KiB chunks, S = 8: 2.20 -> 1.72 ms; 8 KiB chunks: 478 -> 375 us; 32 KiB pieces
+// are at the rate of a plain copy either way).
 //
 // Source slots of one destination block: with S <= 64, lane j of every wave holds
 // src_plan[g*S + j] and rows are picked with a cross-lane shuffle; otherwise each unit reads
 // its entry from memory. The copy is branch-free so the compiler can keep every load of a
-// round in flight (a conditional load or store would force a full wait on the vector
+// piece in flight (a conditional load or store would force a full wait on the vector
 // memory counter): lanes of padding rows (src_plan -1, the tail of a request's last block)
 // load the part's first row, which the workgroup reads anyway, and their stores go through a
 // buffer resource spanning only the destination chunk with an out-of-range offset, which the
 // hardware drops. Padding rows are a suffix of the block, so a part whose first row is
-// padding is all padding and is skipped.
+// padding is all padding: it reads slot 0's row and writes nothing.
 // ------------------------------------------------------------------------------------------
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
@@ -61,7 +70,7 @@ constexpr Policy kPolicies[] = {
     {false, 0},   // 1: plain loads, plain stores
     {true, 2},    // 2: non-temporal loads and stores
     {true, 0},    // 3: non-temporal loads, plain stores
-    {true, 16},   // 4: non-temporal loads, sc1 stores
+    {true, 16},   // 4: non-temporal loads, sc1 stores (the default's kernels)
     {true, 17},   // 5: non-temporal loads, sc0 sc1 stores
     {true, 18},   // 6: non-temporal loads, sc1 nt stores
 };
@@ -85,10 +94,18 @@ __device__ __forceinline__ uint8_t* uniform_ptr(uint8_t* p) {
   return reinterpret_cast<uint8_t*>((static_cast<uint64_t>(hi) << 32) | lo);
 }
 
-template <int kPolicy, bool kSmallS, int kV>
+// Fewest workgroups the items are spread over (where there are as many items): 8 per CU.
+constexpr int kMinCopyGrid = 2048;
+
+// kU units per thread and piece; kW waves per piece (4: the whole workgroup); kWalk: a workgroup
+// may take several items (else the grid has a workgroup for every item).
+template <int kPolicy, bool kSmallS, int kU, int kW, bool kWalk>
 __global__ __launch_bounds__(kCopyThreads) void repack_direct_kernel(CopyArgs a) {
   constexpr Policy pol = kPolicies[kPolicy];
-  constexpr int kRound = kCopyThreads * kV;  // units of one part
+  constexpr int kLanes = 64 * kW;                  // threads that share a piece
+  constexpr int kSide = kCopyThreads / kLanes;     // pieces side by side in the workgroup
+  constexpr int kRound = kLanes * kU;              // units of a piece
+  static_assert(kU == 1 || kSide == 1, "several units per thread: the whole workgroup");
   if (a.counters[3] != 0) return;
   // plans of the full pass; plans of the partial pass too, but not with the freed list of
   // vtoken_repack_free (a partial pass releases its selected sources, not table tails)
@@ -111,7 +128,19 @@ __global__ __launch_bounds__(kCopyThreads) void repack_direct_kernel(CopyArgs a)
   const int parts = (chunk + kRound - 1) / kRound;
   // gp = g * parts + part: the parts of a destination block are consecutive in both orders
   const int used_parts = used * parts;
-  const int64_t items = (int64_t)used_parts * P;
+  const int64_t items = ((int64_t)used_parts * P + kSide - 1) / kSide;   // kSide pieces each
+  // the workgroups that take items (the first ones; the others exit): with pieces below 16 KiB,
+  // enough items each (where there are that many) that the chain of reads at a workgroup's start
+  // is paid once per 32 KiB
+  int grid = a.copy_grid;
+  int64_t w = blockIdx.x;
+  if (kWalk && kU < 4) {
+    int64_t want = items * kU / 8;
+    want = want > kMinCopyGrid ? want : kMinCopyGrid;
+    if (want < grid) grid = static_cast<int>(want);
+    if (w >= grid) return;
+  }
+  if (w >= items) return;
   const int S = a.block_size;
   const uint32_t chunk_bytes = static_cast<uint32_t>(chunk) * 16u;
   const int U = a.row_units;
@@ -119,144 +148,220 @@ __global__ __launch_bounds__(kCopyThreads) void repack_direct_kernel(CopyArgs a)
   // 2 <= U <= 2^12 (checked on the host)
   const uint32_t magic = a.row_magic;
   const bool unit_rows = U == 1;  // 16-byte rows: j = u (the constant would not fit)
-  const int lane = threadIdx.x & 63;
   const int tid = static_cast<int>(threadIdx.x);
-  // (hi, lo) = (plane, gp) for the plane-major order, (gp, plane) for the block-major order
+  const int lane = tid & 63;
+  const int side = kSide == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid / kLanes);
+  const int sub = tid % kLanes;
+  // lanes >= S read plan entry S-1 and never use it
+  const int plan_lane = lane < S ? lane : S - 1;
+
+  // Where a piece lies: (hi, lo) = (plane, gp) in the plane-major order, (gp, plane) in the
+  // block-major one
   const bool plane_major = a.order == 1;
   const int inner = plane_major ? used_parts : P;
-  int64_t w = blockIdx.x;
-  if (items < a.copy_grid) {
-    // fewer items than workgroups: item k runs in workgroup floor(k * grid / items), so the
-    // workgroups without an item are spread through the launch, where the dispatcher has time
-    // to spare, instead of trailing it (Llama-3-8B Random: 103K of 524K, 12 us)
-    const int64_t k = (w * items + a.copy_grid - 1) / a.copy_grid;
-    if (k >= items || (k * a.copy_grid) / items != w) return;
-    w = k;
-  }
-  if (w >= items) return;
-  int hi = static_cast<int>(w / inner);
-  int lo = static_cast<int>(w - (int64_t)hi * inner);
-  const int grid = a.copy_grid;
-  const int step_hi = grid / inner;
-  const int step_lo = grid - step_hi * inner;
-
-  // prefetch of the next item's destination block and plan entry (lanes >= S read entry
-  // S-1 and never use it; the loads are unconditional so no branch splits the copy loop)
-  const int plan_lane = lane < S ? lane : S - 1;
-  int next_gp = plane_major ? lo : hi;
-  int next_g = next_gp / parts;
-  int next_dblk = a.free_list[next_g];
-  int next_pv = kSmallS ? a.src_plan[(int64_t)next_g * S + plan_lane] : -1;
-
-  for (; w < items; w += grid) {
-    const int plane = plane_major ? hi : lo;
-    const int g = next_g;
-    const int part = next_gp - g * parts;
-    const int dblk = __builtin_amdgcn_readfirstlane(next_dblk);
-    const int pv = next_pv;
-    lo += step_lo;
-    hi += step_hi;
-    if (lo >= inner) {
-      lo -= inner;
-      ++hi;
-    }
-    // past the last item the prefetch re-reads item 0's entries (in bounds, unused)
-    next_gp = (w + grid < items) ? (plane_major ? lo : hi) : 0;
-    next_g = next_gp / parts;
-    next_dblk = a.free_list[next_g];
-    if (kSmallS) next_pv = a.src_plan[(int64_t)next_g * S + plan_lane];
-
-    const bool dst_ok = static_cast<unsigned>(dblk) < static_cast<unsigned>(a.num_blocks);
-    const uint8_t* pbase = a.kv + (int64_t)plane * a.plane_bytes;
-    uint8_t* dptr = uniform_ptr(a.kv + (int64_t)plane * a.plane_bytes +
-                                (dst_ok ? (int64_t)dblk * S * a.row_bytes : 0));
-    const __amdgpu_buffer_rsrc_t drsrc =
-        __builtin_amdgcn_make_buffer_rsrc(dptr, 0, dst_ok ? chunk_bytes : 0u, kBufferDword3);
-    const int32_t* plan = a.src_plan + (int64_t)g * S;
-    const int u0 = part * kRound;
-    const int j0 =
-        unit_rows ? u0 : static_cast<int>(__umulhi(static_cast<uint32_t>(u0), magic));
-    const int s0 = kSmallS ? __builtin_amdgcn_readlane(pv, j0)
-                           : __builtin_amdgcn_readfirstlane(plan[j0]);
+  struct Pos {
+    int hi, lo;
+  };
+  const int64_t first = w * kSide + side;
+  const int64_t stride = (int64_t)grid * kSide;
+  Pos p;
+  p.hi = static_cast<int>(first / inner);
+  p.lo = static_cast<int>(first - (int64_t)p.hi * inner);
+  const int step_hi = static_cast<int>(stride / inner);
+  const int step_lo = static_cast<int>(stride - (int64_t)step_hi * inner);
+  struct Piece {
+    int g, part, plane;
+    bool in;
+  };
+  // a position past the last piece (the end of the last item, the item after a workgroup's last)
+  // reads the last piece and writes nothing
+  auto locate = [&](const Pos& at) {
+    Piece c;
+    int gp = plane_major ? at.lo : at.hi;
+    c.plane = plane_major ? at.hi : at.lo;
+    c.in = static_cast<unsigned>(gp) < static_cast<unsigned>(used_parts) &&
+           static_cast<unsigned>(c.plane) < static_cast<unsigned>(P);
+    gp = c.in ? gp : used_parts - 1;
+    c.plane = c.in ? c.plane : P - 1;
+    c.g = parts == 1 ? gp : gp / parts;
+    c.part = gp - c.g * parts;
+    return c;
+  };
+  struct Meta {
+    int dblk;   // destination block
+    int pv;     // this lane's plan entry (S <= 64)
+  };
+  auto load_meta = [&](const Piece& c) {
+    return Meta{a.free_list[c.g], kSmallS ? a.src_plan[(int64_t)c.g * S + plan_lane] : -1};
+  };
+  struct Flight {
+    u32x4 buf[kU];
+    uint32_t off[kU];
+    uint8_t* dptr;
+    uint32_t bytes;
+  };
+  auto load_piece = [&](const Piece& c, const Meta& m, Flight& f) {
+    const int dblk = __builtin_amdgcn_readfirstlane(m.dblk);
+    const bool dst_ok = c.in && static_cast<unsigned>(dblk) < static_cast<unsigned>(a.num_blocks);
+    const uint8_t* pbase = a.kv + (int64_t)c.plane * a.plane_bytes;
+    f.dptr = uniform_ptr(a.kv + (int64_t)c.plane * a.plane_bytes +
+                         (dst_ok ? (int64_t)dblk * S * a.row_bytes : 0));
+    f.bytes = dst_ok ? chunk_bytes : 0u;
+    const int32_t* plan = a.src_plan + (int64_t)c.g * S;
+    const int u0 = c.part * kRound;
+    const int j0 = unit_rows ? u0 : static_cast<int>(__umulhi(static_cast<uint32_t>(u0), magic));
+    int s0 = kSmallS ? __builtin_amdgcn_readlane(m.pv, j0)
+                     : __builtin_amdgcn_readfirstlane(plan[j0]);
     // the part's first row is padding: so is the rest of the part
-    if (static_cast<unsigned>(s0) >= static_cast<unsigned>(a.num_slots)) continue;
-    {
-      int src[kV];
-      int col[kV];
-      uint32_t off[kV];
+    if (static_cast<unsigned>(s0) >= static_cast<unsigned>(a.num_slots)) {
+      if (!kWalk) return false;
+      s0 = 0;
+    }
+    int src[kU];
+    int col[kU];
 #pragma unroll
-      for (int v = 0; v < kV; ++v) {
-        const int u = u0 + v * kCopyThreads + tid;
-        const int j = unit_rows ? u : static_cast<int>(__umulhi(static_cast<uint32_t>(u), magic));
-        col[v] = u - j * U;
-        int s;
-        if (kSmallS) {
-          s = __shfl(pv, j & 63, 64);
-        } else {
-          s = u < chunk ? plan[j] : -1;
-        }
-        const bool ok =
-            (u < chunk) && static_cast<unsigned>(s) < static_cast<unsigned>(a.num_slots);
-        src[v] = ok ? s : s0;
-        off[v] = ok ? static_cast<uint32_t>(u) * 16u : kDropOffset;
+    for (int v = 0; v < kU; ++v) {
+      const int u = u0 + v * kLanes + sub;
+      const int j = unit_rows ? u : static_cast<int>(__umulhi(static_cast<uint32_t>(u), magic));
+      col[v] = u - j * U;
+      int s;
+      if (kSmallS) {
+        s = __shfl(m.pv, j & 63, 64);
+      } else {
+        s = u < chunk ? plan[j] : -1;
       }
-      u32x4 buf[kV];
+      const bool ok = (u < chunk) && static_cast<unsigned>(s) < static_cast<unsigned>(a.num_slots);
+      src[v] = ok ? s : s0;
+      f.off[v] = ok ? static_cast<uint32_t>(u) * 16u : kDropOffset;
+    }
 #pragma unroll
-      for (int v = 0; v < kV; ++v) {
-        buf[v] = load16<pol.load_nt>(
-            reinterpret_cast<const u32x4*>(pbase + (int64_t)src[v] * a.row_bytes) + col[v]);
-      }
+    for (int v = 0; v < kU; ++v) {
+      f.buf[v] = load16<pol.load_nt>(
+          reinterpret_cast<const u32x4*>(pbase + (int64_t)src[v] * a.row_bytes) + col[v]);
+    }
+    return true;
+  };
+  auto store_piece = [&](const Flight& f) {
+    const __amdgpu_buffer_rsrc_t drsrc =
+        __builtin_amdgcn_make_buffer_rsrc(f.dptr, 0, f.bytes, kBufferDword3);
 #pragma unroll
-      for (int v = 0; v < kV; ++v) {
-        __builtin_amdgcn_raw_buffer_store_b128(buf[v], drsrc, off[v], 0, pol.store_aux);
-      }
+    for (int v = 0; v < kU; ++v) {
+      __builtin_amdgcn_raw_buffer_store_b128(f.buf[v], drsrc, f.off[v], 0, pol.store_aux);
+    }
+  };
+
+  // Two pieces in flight. Vector-memory operations retire in order, so the plan entries of the
+  // piece after next are read before the next one's loads: a wait for them then waits for no
+  // row.
+  Flight x, y;
+  Piece c = locate(p);
+  Meta m = load_meta(c);
+  if (!kWalk || w + grid >= items) {
+    if (load_piece(c, m, x)) store_piece(x);
+    return;
+  }
+  auto issue = [&](Flight& f) {
+    p.hi += step_hi;
+    p.lo += step_lo;
+    if (p.lo >= inner) {
+      p.lo -= inner;
+      ++p.hi;
+    }
+    const Piece cn = locate(p);
+    const Meta mn = load_meta(cn);
+    __builtin_amdgcn_sched_barrier(0);
+    load_piece(c, m, f);
+    __builtin_amdgcn_sched_barrier(0);
+    c = cn;
+    m = mn;
+  };
+  issue(x);
+  for (;;) {
+    issue(y);
+    store_piece(x);
+    if ((w += grid) + grid >= items) {
+      store_piece(y);
+      return;
+    }
+    issue(x);
+    store_piece(y);
+    if ((w += grid) + grid >= items) {
+      store_piece(x);
+      return;
     }
   }
 }
 
-// Default launch: one workgroup per work item, for as many items as the buffers can hold
-// (the device-side count is not known on the host), capped at kMaxCopyGrid workgroups; the
-// kernel's grid-stride loop covers the rest, and with fewer items than workgroups it spreads
-// the items over the grid (the workgroups left without one exit at once). Measured on
-// MI355X, one item per workgroup beats a persistent grid sized from occupancy: the hardware
-// dispatcher refills CUs as workgroups retire, while a persistent wave has to drain its
-// stores before its next item's loads.
-constexpr int64_t kMaxCopyGrid = 1 << 19;
+// Default launch: the device-side count of items is not known on the host, only how many the
+// buffers can hold, and every workgroup is dispatched even when the plan admits nothing, at
+// about 4.5 per ns: an empty pass of 2^19 workgroups took 110 us, and a pass of 10K pieces with
+// room for 230K (Llama-3-8B, 512 sources) 165 us for a copy of 110. So the grid has a workgroup
+// for every item up to kFewItems, above that one for every eighth, up to a cap, and the kernel
+// walks the rest. For 32 KiB pieces, caps of 2^17, 2^16, 2^15 and 2^14 cost a full Llama-3-8B
+// copy (407K pieces, room for 1.3M) 0, 0.2%, 0.4% and 0.8% against one workgroup per piece; for
+// 4 KiB ones (Llama-3-70B fp8 at TP 8, 1.7M pieces) 2^16 and 2^15 cost 0.3% and 0.7%. The copy of a full
+// pass (vtoken_repack_free) takes the larger cap of its size, vtoken_repack, which also serves
+// the partial passes that often move little or nothing, half of it (empty pass: 15 us at 2^16,
+// 8 us at 2^15). Spreading the workgroups with items over the launch instead, so that the
+// dispatch of the empty ones overlaps the copy, makes them slower: 49 destination blocks in a
+// room for 28K took 37 us so, 5.5 us with the empty ones behind them.
+constexpr int kFewItems = 1 << 13;
+constexpr int kMaxCopyGrid = 1 << 17;        // pieces of 16 KiB and more
+constexpr int kMaxCopyGridSmall = 1 << 16;   // smaller pieces
 
-template <void (*kKernel)(CopyArgs)>
-hipError_t launch_kernel(const CopyArgs& a_in, int64_t items, int grid, hipStream_t stream) {
-  if (grid <= 0) grid = static_cast<int>(items < kMaxCopyGrid ? items : kMaxCopyGrid);
+template <int kPolicy, int kU, int kW>
+hipError_t launch_direct(const CopyArgs& a_in, int grid, hipStream_t stream) {
+  // pieces: every (part of a destination block, plane) the buffers can hold; the kernel
+  // indexes parts with 32-bit integers
+  constexpr int kRound = 64 * kW * kU;
+  constexpr int kSide = kCopyThreads / 64 / kW;
   CopyArgs a = a_in;
+  const int64_t parts = (a.chunk_units + kRound - 1) / kRound;
+  if ((int64_t)a.max_used * parts > 0x7fffffff) return hipErrorInvalidValue;
+  const int64_t items = ((int64_t)a.max_used * parts * a.num_planes + kSide - 1) / kSide;
+  // a launch with a workgroup for every item takes the kernel without the walk, whose second set
+  // of rows costs registers (92 for 52 at kU = 8) and so workgroups in flight (3,712 pieces out
+  // of the caches: 25 us, 28 with it); with small pieces only if all workgroups are resident at
+  // once
+  bool walk = kPolicy != 0;
+  if (grid <= 0) {
+    const int cap = (kU >= 4 ? kMaxCopyGrid : kMaxCopyGridSmall) / (a.num_reqs > 0 ? 1 : 2);
+    const int64_t most = items / 8 > kFewItems ? items / 8 : kFewItems;
+    grid = static_cast<int>(most < cap ? (items < most ? items : most) : cap);
+    walk |= items > (kU >= 4 ? grid : kMinCopyGrid);
+  } else {
+    walk = true;
+  }
   a.copy_grid = grid;
   // the freed list's workgroups follow the copy's
   const int64_t total = (int64_t)grid + a.num_reqs;
   if (total <= 0) return hipSuccess;
-  hipLaunchKernelGGL(kKernel, dim3(static_cast<unsigned>(total)), dim3(kCopyThreads), 0, stream,
-                     a);
-  return hipGetLastError();
-}
-
-template <int kPolicy, int kV>
-hipError_t launch_direct(const CopyArgs& a, int grid, hipStream_t stream) {
-  // work items: every (part of a destination block, plane) the buffers can hold; the kernel
-  // indexes parts with 32-bit integers
-  const int64_t parts = (a.chunk_units + kCopyThreads * kV - 1) / (kCopyThreads * kV);
-  if ((int64_t)a.max_used * parts > 0x7fffffff) return hipErrorInvalidValue;
-  const int64_t items = (int64_t)a.max_used * parts * a.num_planes;
-  if (a.block_size <= 64) {
-    return launch_kernel<repack_direct_kernel<kPolicy, true, kV>>(a, items, grid, stream);
+  const dim3 g(static_cast<unsigned>(total)), t(kCopyThreads);
+  if constexpr (kPolicy == 0) {
+    if (!walk) {
+      const auto kernel = a.block_size <= 64 ? repack_direct_kernel<kPolicy, true, kU, kW, false>
+                                             : repack_direct_kernel<kPolicy, false, kU, kW, false>;
+      hipLaunchKernelGGL(kernel, g, t, 0, stream, a);
+      return hipGetLastError();
+    }
   }
-  return launch_kernel<repack_direct_kernel<kPolicy, false, kV>>(a, items, grid, stream);
+  const auto kernel = a.block_size <= 64 ? repack_direct_kernel<kPolicy, true, kU, kW, true>
+                                         : repack_direct_kernel<kPolicy, false, kU, kW, true>;
+  hipLaunchKernelGGL(kernel, g, t, 0, stream, a);
+  return hipGetLastError();
 }
 
 template <int kPolicy>
 hipError_t launch_policy(const CopyArgs& a, int grid, hipStream_t stream) {
-  // enough 16-byte units per thread to cover one chunk, at most 8
+  // enough 16-byte units per thread to cover one chunk, at most 8; chunks below a workgroup's
+  // 256 units go to the fewest waves that cover them
   const int per_thread = a.chunk_units / kCopyThreads;
-  if (per_thread >= 8) return launch_direct<kPolicy, 8>(a, grid, stream);
-  if (per_thread >= 4) return launch_direct<kPolicy, 4>(a, grid, stream);
-  if (per_thread >= 2) return launch_direct<kPolicy, 2>(a, grid, stream);
-  return launch_direct<kPolicy, 1>(a, grid, stream);
+  if (per_thread >= 8) return launch_direct<kPolicy, 8, 4>(a, grid, stream);
+  if (per_thread >= 4) return launch_direct<kPolicy, 4, 4>(a, grid, stream);
+  if (per_thread >= 2) return launch_direct<kPolicy, 2, 4>(a, grid, stream);
+  if (a.chunk_units > 128) return launch_direct<kPolicy, 1, 4>(a, grid, stream);
+  if (a.chunk_units > 64) return launch_direct<kPolicy, 1, 2>(a, grid, stream);
+  return launch_direct<kPolicy, 1, 1>(a, grid, stream);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -603,11 +708,11 @@ hipError_t launch_repack(const CopyArgs& a_in, int variant, int grid, int order,
   CopyArgs a = a_in;
   a.order = order;
   switch (variant) {
-    case 0: return launch_policy<0>(a, grid, stream);
+    case 0:
+    case 4: return launch_policy<0>(a, grid, stream);
     case 1: return launch_policy<1>(a, grid, stream);
     case 2: return launch_policy<2>(a, grid, stream);
     case 3: return launch_policy<3>(a, grid, stream);
-    case 4: return launch_policy<4>(a, grid, stream);
     case 5: return launch_policy<5>(a, grid, stream);
     case 6: return launch_policy<6>(a, grid, stream);
     default: return hipErrorInvalidValue;
