@@ -374,13 +374,14 @@ vtoken_status vtoken_append_slots(int32_t num_reqs, const int32_t* append_indptr
  * and query head qh (GQA: KV head qh / (num_q_heads / num_kv_heads)),
  *   out[r][qh] = softmax(scale * q[r][qh] . K[slot]^T) @ V[slot] over the slots of r,
  * K and V being the layer's K and V planes (float32 math; zeros for a request with no slots).
- * Flash-decoding: splits of 32 KiB of K per KV head (32768 / (head_dim * elem_bytes) tokens;
- * 64 KiB for 2-byte caches with 8 query heads per KV head, or when max_tokens spans 64 or
- * more 32 KiB splits), then a merge; the workspace
+ * Flash-decoding: splits of 1, 2, 4 or 8 times 32 KiB of K per KV head (32768 / (head_dim *
+ * elem_bytes) tokens each; chosen from the batch's size and max_tokens), then, where a request
+ * may have several, a merge; the workspace
  * holds the split partials and is overwritten by every call (calls sharing it must be
  * stream-ordered). A request with more slots than max_tokens provides for is never
- * truncated: its outputs are NaN, unless its slots still fit the ceil(max_tokens / split)
- * splits, which are all computed. A slot outside the pool (negative
+ * truncated: its outputs are NaN, unless its slots still fit max_tokens rounded up to a multiple
+ * of 32 KiB of K (64 KiB for 2-byte caches with 8 query heads per KV head, or when max_tokens
+ * spans 64 or more times 32 KiB), which are all computed. A slot outside the pool (negative
  * or >= num_blocks * block_size) is never dereferenced; its request's outputs are NaN. A
  * request whose slot range is malformed (slot_indptr[r] < 0, or a negative count:
  * slot_indptr[r+1] < slot_indptr[r], or slot_count[r] < 0) reads no slot and gets NaN

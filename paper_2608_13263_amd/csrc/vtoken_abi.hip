@@ -414,15 +414,19 @@ vtoken_status paged_decode(const vtoken_cache* cache, const vtoken_decode* d, in
   a.kv_kind = kind;
   a.num_slots = cache->num_blocks * cache->block_size;
   a.num_reqs = num_reqs;
-  const int split = vtoken::decode_split_tokens_w(
-      D, cache->elem_bytes, vtoken::decode_waves_for(D, cache->elem_bytes, g, d->max_tokens));
-  a.split_tokens = split;
-  // in 64 bits: max_tokens may lie within one split of INT32_MAX
+  a.max_count = vtoken::decode_max_count(D, cache->elem_bytes, g, d->max_tokens);
+  // (64-bit: max_tokens may lie within one unit of INT32_MAX)
+  const int64_t split =
+      (int64_t)vtoken::decode_unit_tokens(D, cache->elem_bytes) *
+      vtoken::decode_split_units(D, cache->elem_bytes, (int64_t)num_reqs * cache->num_kv_heads,
+                                 d->max_tokens);
+  a.split_tokens = static_cast<int32_t>(split);
   a.splits = d->max_tokens > 0
                  ? static_cast<int32_t>(((int64_t)d->max_tokens + split - 1) / split)
                  : 1;
-  const int64_t grid_splits = vtoken::decode_grid_splits(a.splits);
-  if ((int64_t)num_reqs * cache->num_kv_heads * grid_splits > INT32_MAX ||
+  const int64_t groups =
+      vtoken::decode_grid_groups((int64_t)num_reqs * vtoken::decode_grid_splits(a.splits));
+  if (groups * cache->num_kv_heads > INT32_MAX ||
       (int64_t)num_reqs * d->num_q_heads > INT32_MAX) {
     return VTOKEN_ERR_SHAPE;
   }

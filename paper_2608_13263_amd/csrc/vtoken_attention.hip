@@ -5,11 +5,11 @@
 //   slot_map_kernel      one workgroup per request: wave-ballot compaction of token_slot,
 //                        the live tokens' slots in logical order (Sec. 3.4: the slot mapping
 //                        is built through the token table, once per token)
-//   decode_split_kernel  one workgroup per (request, KV head, split of 32 KiB of K: 32768 /
-//                        (D * element bytes) tokens): scores and the weighted sum of V of the
-//                        G query heads that share the KV head, both on the matrix cores, with
-//                        a split-local softmax (flash-decoding partials)
-//   decode_combine_kernel  one workgroup per (request, query head): merges the splits
+//   decode_split_kernel  one workgroup per (request, KV head, split): scores and the weighted sum
+//                        of V of the G query heads that share the KV head, both on the matrix
+//                        cores, with a running softmax (flash-decoding partials)
+//   decode_combine_kernel  one workgroup per (request, query head): merges the splits (no launch
+//                        where one split covers every request)
 //
 // Decode attention is HBM-bound (2G flops per byte of K/V). Both products are small dense
 // contractions (16 tokens x D x the G heads of a KV head, and their transposes) and run on
@@ -18,6 +18,7 @@
 
 #include <atomic>
 #include <mutex>
+#include <type_traits>
 
 #include "vtoken_internal.h"
 
@@ -224,6 +225,18 @@ __device__ __forceinline__ u32x4 v_row16(typename Piece<kKind>::type w) {
   }
 }
 
+// 16 (V elements) x 16 tokens x 16 (columns), for the rounds of one 16-token tile.
+template <int kKind>
+__device__ __forceinline__ f32x4 value_mfma4(i16x4 v, i16x4 p, f32x4 acc) {
+  if constexpr (kKind == 0) {
+    typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+    return __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(f16x4, v),
+                                                 __builtin_bit_cast(f16x4, p), acc, 0, 0, 0);
+  } else {
+    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(v, p, acc, 0, 0, 0);
+  }
+}
+
 // LDS transpose read of gfx950 (ds_read_b64_tr_b16): in each group of 16 lanes, lane
 // 4a + b receives element b of the four 16-bit values addressed by lanes a, a+4, a+8 and
 // a+12 of its group (in that order).
@@ -277,337 +290,434 @@ __device__ __forceinline__ float lanes_reduce(float x) {
   return xor_combine<32, kMax>(x);
 }
 
-// Minimum waves per SIMD the decode kernels are compiled for. The fp8 geometries with
-// head_dim 64 or 128, and the 16-bit ones up to head_dim 128, come out a few registers above
-// the four-wave budget (128 registers); held to it they do not spill (fp8: 5-10% faster).
-// Elsewhere the compiler's choice stands (fp8 with head_dim 32 or 256 would spill).
-constexpr int decode_min_waves(int kind, int head_dim) {
-  return kind == 2 ? (head_dim == 64 || head_dim == 128 ? 4 : 1) : (head_dim <= 128 ? 4 : 1);
+// Requests whose outputs no split decides: without slots (zeros), and those whose slot range is
+// malformed (the split kernel reads nothing for them) or holds more slots than max_tokens
+// provides for (NaN).
+__device__ __forceinline__ bool decode_fixed_output(const AttnArgs& a, int s0, int c) {
+  return s0 < 0 || c <= 0 || c > a.max_count;
 }
+
+// Waves of a split workgroup.
+constexpr int kSplitWaves = kDecodeSplitWaves;
 
 // Split kernel of the paged decode, both products on the matrix cores.
 //
-// kKind: element type; kD: head_dim (32, 64, 128, 256); kG: query heads per KV head (1, 2,
-// 4, 8; smaller groups leave operand columns as zero padding).
-//
-// One workgroup (kWaves = 4 waves, 8 for 16-bit caches at kG = 8) covers kSplit = kWaves *
-// 8192 / (kD * element bytes) tokens of one (request, KV head); wave w owns tokens
-// [w*kTW, (w+1)*kTW), kTW = kSplit / kWaves, and computes
-// for them, on the matrix cores (MFMA 16x16x32, fp16 for fp16 caches, bf16 otherwise; fp8
-// widened to bf16):
+// kKind: element type; kD: head_dim (32, 64, 128, 256). One workgroup of four waves covers
+// a.split_tokens tokens (a whole number of rounds) of one (request, KV head) and its 1, 2, 4 or 8
+// query heads; in round i wave w takes the kIT tokens from (i * 4 + w) * kIT on, 4 KiB of K and
+// 4 KiB of V (8 KiB each with 512-byte head rows), and computes for them, on the matrix cores
+// (MFMA 16x16x32, fp16 for fp16 caches, bf16 otherwise; fp8 widened to bf16):
 //   scores  S[token][col] = K_tile (16 x kD) . Q2^T (kD x 16). The float32 query is split into
-//           high and low 16-bit parts (q = hi + lo to ~2^-17): column c < 8 of Q2 is the high
-//           part of head c, column c + 8 its low part (zero for c >= kG), so one product
-//           carries both and the score of head c is S[.][c] + S[.][c + 8] (float32 accuracy);
-//   weights p = exp(score - m_w) with the wave's own maximum m_w per head, l_w = sum of p;
-//   values  O2[row][d] = P2 (16 x 32 tokens) . V (32 tokens x 16 elements) per 16-element
-//           chunk, row c < 8 of P2 the high part of head c's weights, row c + 8 their low
-//           part, so O_w[c] = O2[c] + O2[c + 8]. V goes through a per-wave LDS window of 32
-//           rows, one 32-token k-step at a time (16-bit rows, padded by 32 bytes against bank
-//           conflicts), and comes back in operand layout by transpose reads. The operand
-//           layout fixes which tokens a lane holds: lane l has column l%16 and, of each
-//           32-token chunk, tokens 4*(l/16)..+3 of its first 16-token tile and the same of its
-//           second; the V rows are read in that order.
-// The waves are merged with the usual max-rescaling into the split's record.
-// Every thread issues all of its K and V loads (128 + 128 bytes) before any arithmetic.
+//           high and low 16-bit parts (q = hi + lo to ~2^-17; 2^-22 in fp16): column c < 8 of Q2
+//           is the high part of head c, column c + 8 its low part (zero past the last head), so
+//           one product carries both and the score of head c is S[.][c] + S[.][c + 8]. For bf16
+//           operands a third part (to 2^-26) takes the scores' share out of the outputs' error
+//           (3.1e-6 -> 1.9e-6 relative): with at most four heads it has columns c + 4, with eight
+//           (kG8) a second product;
+//   weights p = exp(score - m), m the wave's running maximum per head; where m grows, the sums so
+//           far are scaled down;
+//   values  O2[d][col] += V^T (16 elements x 32 tokens) . P2^T (32 tokens x 16) per 16-element
+//           chunk, column c < 8 of P2^T the high part of head c's weights, column c + 8 their low
+//           part, so O[.][c] = O2[.][c] + O2[.][c + 8], and a lane's column of O is that of its
+//           scores: scaling it takes no exchange between lanes. The operand layout fixes which
+//           tokens a lane holds: lane l has column l%16 and, of each 32-token step, tokens
+//           4*(l/16)..+3 of its first 16-token tile and the same of its second; the V rows are
+//           read in that order.
+// The waves are merged with the usual max-rescaling into the split's record, or, where one split
+// covers every request (a.splits == 1), into the outputs.
+//
+// Bound: HBM (with the arithmetic taken out, the loads alone run 3-5% faster). K and V are read
+// the same way, 16 bytes per lane with consecutive lanes on one head row, so that every line is
+// used by one non-temporal load (read in operand order, a line of K is split over two loads,
+// which only plain loads serve at all well: 6.2 against 6.95 TB/s over a large cache); both go
+// through this wave's LDS window into operand order (K rows padded by 16 bytes, V rows, read back
+// by transpose reads, by 32, against bank conflicts). The next round's K loads are issued as soon
+// as K is in the window, its V loads as soon as V is: the registers hold one round and a wave has
+// 4 to 8 KiB in flight at any time, three waves per SIMD. Twice that per wave (8 KiB, two waves
+// per SIMD) and four waves per SIMD measured the same within 2%; held to three waves, 8 KiB
+// spills and is 10-20% slower. The query operands, the merge of the waves and the split record
+// are paid once per split: in workgroups of one round they were over half of the 1,400
+// instructions per wave, which bound fp8 batches.
+// Measured per layer, merge included, against one round per workgroup and K in operand order:
+// bf16, 64 requests of 678-2,521 slots, 8 heads x 128, G = 4 86.5 -> 78 us (421 MB); fp8, 29
+// requests of 5,043-19,788, G = 8 169 -> 143 us (735 MB); bf16, 4 x 256, 18 requests of 6K
+// 135 -> 83 us (437 MB).
 // Non-finite K or V values are outside the contract (a zero weight times an infinite value
 // gives NaN).
-template <int kKind, int kD, int kG, int kWaves>
-__global__ __launch_bounds__(64 * kWaves)
-__attribute__((amdgpu_waves_per_eu(decode_min_waves(kKind, kD))))
+template <int kKind, int kD, bool kG8>
+__global__ __launch_bounds__(64 * kSplitWaves)
+__attribute__((amdgpu_waves_per_eu(kD * (kKind == 2 ? 1 : 2) > 256 ? 2 : 3)))
 void decode_split_kernel(AttnArgs a) {
-  using PieceT = typename Piece<kKind>::type;
   using OpT = typename ScoreOp<kKind>::type;
   using ElemT = typename ScoreOp<kKind>::elem;
   constexpr int kElem = kKind == 2 ? 1 : 2;
-  constexpr int kChunks = kD / 32;                   // score k-steps
-  constexpr int kSplit = decode_split_tokens_w(kD, kElem, kWaves);
+  constexpr int kWaves = kSplitWaves;
   constexpr int kThreads = 64 * kWaves;
-  constexpr int kTW = kSplit / kWaves;               // tokens per wave: 16 .. 256
-  constexpr int kTiles = kTW / 16;                   // 16-token score tiles per wave
-  constexpr int kKC = (kTiles + 1) / 2;              // 32-token value k-steps per wave
+  constexpr int kRow = kD * kElem;                   // bytes of a head row
+  constexpr int kIT = decode_wave_tokens(kD, kElem);  // tokens of a wave per round: 16 .. 128
+  constexpr int kStep = kWaves * kIT;                // tokens of a round
+  constexpr int kTiles = kIT / 16;                   // 16-token score tiles
+  constexpr int kChunks = kD / 32;                   // score k-steps
+  constexpr int kKC = (kTiles + 1) / 2;              // 32-token value k-steps
   constexpr int kDC = kD / 16;                       // 16-element value chunks
-  constexpr int kPerV = kKind == 2 ? 16 : kPer;      // V elements per lane load: 16 bytes
-  constexpr int kLanesV = kD / kPerV;                // V load: lanes per token row
-  constexpr int kTokV = 64 / kLanesV;                // V load: tokens per wave pass
-  constexpr int kItV = kTW / kTokV;                  // V load: pieces per lane
-  constexpr int kWin = kTW < 32 ? kTW : 32;          // V rows a wave stages per k-step
-  constexpr int kItW = kWin / kTokV;                 // V pieces per lane per k-step
-  constexpr int kRowB = kD * 2 + 32;                 // LDS bytes per V row
-  static_assert(kTiles * 16 == kTW && kItW * kKC == kItV && kItW * kTokV == kWin,
-                "split geometry");
-  static_assert(kG >= 1 && kG <= 8, "the high and low parts fill the 16 operand columns");
-  constexpr int kVB = kWaves * kWin * kRowB;
-  constexpr int kMergeB = kWaves * kG * (kD + 2) * 4;
-  constexpr int kLdsB = kVB > kMergeB ? kVB : kMergeB;
+  constexpr int kLanes = kRow / 16;                  // loads: lanes per token row
+  constexpr int kTok = 64 / kLanes;                  // loads: tokens per instruction
+  constexpr int kLd = kIT / kTok;                    // loads per operand and round
+  constexpr int kSR = (kIT + 63) / 64;               // slot registers
+  constexpr int kWin = kIT < 32 ? kIT : 32;          // V rows staged per k-step
+  constexpr int kLdW = kWin / kTok;                  // V loads per k-step
+  constexpr int kRowK = kRow + 16;                   // LDS bytes per K row
+  constexpr int kRowV = kD * 2 + 32;                 // LDS bytes per V row (16-bit)
+  static_assert(kLdW * kKC == kLd && kLdW * kTok == kWin, "round geometry");
+  constexpr int kWinB = kIT * kRowK > kWin * kRowV ? kIT * kRowK : kWin * kRowV;
+  constexpr int kRec = kD + 4;                       // merge: m, l, padding, kD values
+  constexpr int kMergeB = kWaves * 8 * kRec * 4;
+  constexpr int kLdsB = kWaves * kWinB > kMergeB ? kWaves * kWinB : kMergeB;
   __shared__ __attribute__((aligned(16))) uint8_t lds[kLdsB];
+  constexpr bool kThird = kKind != 0;                // bf16 operands: a third query part
+  constexpr int kHeads = kThird && !kG8 ? 4 : 8;     // heads side by side in the columns
+  constexpr int kQ = kThird && kG8 ? 2 : 1;          // query operands per chunk
+  __shared__ OpT q_s[kChunks * kQ][64];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = tid >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int G = a.num_q_heads / a.num_kv_heads;   // query heads per KV head
   // the grid holds decode_grid_splits(a.splits) split slots per (request, KV head); one past
   // a.splits (a count rounded up to an odd one) returns at once
   const int gs = decode_grid_splits(a.splits);
-  const int split = blockIdx.x % gs;
-  const int h = (blockIdx.x / gs) % a.num_kv_heads;
-  const int r = blockIdx.x / (gs * a.num_kv_heads);
+  const int H = a.num_kv_heads;
+  int split, h, r;
+  if constexpr (kRow < 128) {
+    // head rows shorter than a 128-byte line share it: the heads of a split run on one XCD, eight
+    // workgroups apart (fp8, 4 and 8 heads x 32: 28.5 -> 19.7 us, 31.7 -> 21.7 us; with longer
+    // rows the heads of a split at a time cost 2-5%)
+    const int oct = blockIdx.x / (8 * H);
+    const int x = blockIdx.x - oct * 8 * H;
+    const int rs = oct * 8 + x % 8;
+    h = x / 8;
+    r = rs / gs;
+    split = rs - r * gs;
+  } else {
+    split = blockIdx.x % gs;
+    h = (blockIdx.x / gs) % H;
+    r = blockIdx.x / (gs * H);
+  }
   if (r >= a.num_reqs || split >= a.splits) return;
   const int s0 = a.slot_indptr[r];
   const int c = a.slot_count != nullptr ? a.slot_count[r] : a.slot_indptr[r + 1] - s0;
-  const int t0 = split * kSplit;
-  if (t0 >= c || s0 < 0) return;
-  const int nt = c - t0 < kSplit ? c - t0 : kSplit;
+  const int64_t qh0 = (int64_t)r * a.num_q_heads + h * G;   // first query head's row
+  if (decode_fixed_output(a, s0, c)) {   // written here if there is no merge, else there
+    const float fill = c == 0 && s0 >= 0 ? 0.f : __builtin_nanf("");
+    if (a.splits > 1) return;
+    for (int i = tid; i < G * kD; i += kThreads) a.out[qh0 * kD + i] = fill;
+    return;
+  }
+  // the last split takes what is left (up to a.max_count)
+  const int t0 = split * a.split_tokens;
+  if (t0 >= c) return;
+  const int nt = split + 1 < a.splits && c - t0 > a.split_tokens ? a.split_tokens : c - t0;
   const int* slots = a.slots + s0 + t0;
   const uint8_t* kplane = a.kv + (int64_t)(2 * a.layer) * a.plane_bytes;
   const uint8_t* vplane = kplane + a.plane_bytes;
-  const int64_t head0 = (int64_t)h * kD * kElem;
   const int grp = lane >> 4;    // operand k-group / result row group
-  const int row = lane & 15;    // token of a tile (K operand) / column (Q) / row (P)
-  const int wt0 = wave * kTW;   // first token of this wave
+  const int row = lane & 15;    // token of a tile (K operand) / column (Q, P, results)
+  const int wt0 = wave * kIT;   // this wave's first token of round 0
+  const int rounds = wt0 < nt ? (nt - wt0 + kStep - 1) / kStep : 0;
+  const bool low = row >= 8;          // this lane's column holds low parts
+  const int head = row & (kHeads - 1);
+  const bool real = head < G;         // column of a query head (else zero padding)
 
-  const bool low = row >= 8;          // this lane's column / P row holds low parts
-  const bool real = (row & 7) < kG;   // column / P row of a query head (else zero padding)
-  // The query operand of column `row` is head row % 8 (padding columns re-read head 0: the
-  // load is unconditional, since a conditional load would wait for every outstanding K/V
-  // load). Every wave needs the same operands: they are built once per workgroup into LDS and
-  // read after a barrier.
+  // Slot indices of round i: lane l holds token l (and l + 64, ..) of the wave's; tokens past the
+  // split's end re-read its last one
+  struct Slots {
+    int s[kSR];
+  };
+  auto load_slots = [&](int i) {
+    Slots x;
+#pragma unroll
+    for (int q = 0; q < kSR; ++q) {
+      const int t = wt0 + i * kStep + q * 64 + lane;
+      x.s[q] = slots[t < nt ? t : nt - 1];
+    }
+    return x;
+  };
+  bool bad = false;   // a slot outside the pool: never dereferenced, poisons the request
+  int ls[kLd];        // slots of this lane's rows
+  auto spread_slots = [&](Slots x) {
+#pragma unroll
+    for (int q = 0; q < kSR; ++q) {
+      const bool ok = static_cast<unsigned>(x.s[q]) < static_cast<unsigned>(a.num_slots);
+      bad |= !ok;
+      x.s[q] = ok ? x.s[q] : 0;
+    }
+#pragma unroll
+    for (int k = 0; k < kLd; ++k) {
+      ls[k] = __shfl(x.s[k * kTok / 64], (k * kTok + lane / kLanes) & 63, 64);
+    }
+  };
+  const int64_t lane0 = (int64_t)h * kRow + (lane % kLanes) * 16;
+  auto load_rows = [&](const uint8_t* plane, u32x4 (&x)[kLd]) {
+#pragma unroll
+    for (int k = 0; k < kLd; ++k) {
+      x[k] = __builtin_nontemporal_load(
+          reinterpret_cast<const u32x4*>(plane + ((int64_t)ls[k] * a.row_bytes + lane0)));
+    }
+  };
+
+  // ---- the query values and the first two rounds' slots, then the first round's K and V loads;
+  // the query operands are built while those are in flight
   // The head dims of a k-chunk's lane group: any assignment gives the same dot products as
   // long as q and K use the same one. fp8 pairs the chunks (2c, 2c+1) so that a lane's two
-  // 8-byte K pieces are 16 contiguous bytes, read by one load.
+  // 8-byte K pieces are 16 contiguous bytes, read by one LDS read.
   constexpr bool kPairK = kKind == 2 && kChunks % 2 == 0;
   auto head_dim_of = [&](int ch, int e) {
     return kPairK ? (ch >> 1) * 64 + grp * 16 + (ch & 1) * 8 + e : ch * 32 + grp * kPer + e;
   };
-  __shared__ OpT q_s[kChunks][64];
-  // ---- loads in two rounds: the query values and every slot index this lane needs, then
-  // (once the slots are in) every K and V load back to back; the query operands are built
-  // while those are in flight. The vector-memory counter retires loads in order, so a slot
-  // read issued after a K load would hold that slot's K pieces until the earlier K load
-  // returned: interleaving slot reads with K and V loads cost a round trip per tile.
+  Slots cur = load_slots(0);
+  Slots nxt = load_slots(1);
   constexpr int kQC = (kChunks + kWaves - 1) / kWaves;   // query chunks a wave builds
-  const float* qrow =
-      a.q + ((int64_t)r * a.num_q_heads + h * kG + (real ? row & 7 : 0)) * kD;
+  const float* qrow = a.q + (qh0 + (real ? head : 0)) * kD;
   float qraw[kQC][kPer];
 #pragma unroll
-  for (int c = 0; c < kQC; ++c) {
+  for (int x = 0; x < kQC; ++x) {
     // unconditional (a chunk past the last re-reads the last one, unused)
-    const int ch = wave + c * kWaves < kChunks ? wave + c * kWaves : kChunks - 1;
+    const int ch = wave + x * kWaves < kChunks ? wave + x * kWaves : kChunks - 1;
 #pragma unroll
-    for (int e = 0; e < kPer; ++e) qraw[c][e] = qrow[head_dim_of(ch, e)];
+    for (int e = 0; e < kPer; ++e) qraw[x][e] = qrow[head_dim_of(ch, e)];
   }
-  // slot indices of this lane's K tiles and V pieces; tokens past the split's end re-read
-  // its last token
-  int ksl[kTiles];
-#pragma unroll
-  for (int i = 0; i < kTiles; ++i) {
-    const int t = wt0 + i * 16 + row;
-    ksl[i] = slots[t < nt ? t : nt - 1];
-  }
-  const int vpiece = lane % kLanesV;
-  int vsl[kItV];
-#pragma unroll
-  for (int i = 0; i < kItV; ++i) {
-    const int t = wt0 + lane / kLanesV + i * kTokV;
-    vsl[i] = slots[t < nt ? t : nt - 1];
-  }
-  // (the scheduler keeps these reads ahead of the K and V loads, and those ahead of the query
-  // operands' arithmetic)
   __builtin_amdgcn_sched_barrier(0);
-
-  // ---- all K and V loads
-  PieceT kw[kTiles][kChunks];
-  bool kok[kTiles];
-#pragma unroll
-  for (int i = 0; i < kTiles; ++i) {
-    const int sl = ksl[i];
-    kok[i] = static_cast<unsigned>(sl) < static_cast<unsigned>(a.num_slots);
-    const uint8_t* row_base = kplane + (int64_t)(kok[i] ? sl : 0) * a.row_bytes + head0;
-    if constexpr (kPairK) {
-#pragma unroll
-      for (int p = 0; p < kChunks / 2; ++p) {
-        const u32x4 w = *reinterpret_cast<const u32x4*>(row_base + p * 64 + grp * 16);
-        kw[i][2 * p] = PieceT{w.x, w.y};
-        kw[i][2 * p + 1] = PieceT{w.z, w.w};
-      }
-    } else {
-      const uint8_t* base = row_base + grp * kPer * kElem;
-#pragma unroll
-      for (int ch = 0; ch < kChunks; ++ch) {
-        kw[i][ch] = *reinterpret_cast<const PieceT*>(base + ch * 32 * kElem);
-      }
-    }
-  }
-  // V rows: 16 bytes per lane (8 elements at 16 bits, 16 fp8), a whole head row per kLanesV
-  // lanes, read with non-temporal loads (each line is used by one instruction; measured
-  // +2-6% over plain loads). The K pieces above stay plain: in the matrix-core operand order
-  // a row's line is split over two instructions, and non-temporal K loads were slower.
-  u32x4 vw[kItV];
-#pragma unroll
-  for (int i = 0; i < kItV; ++i) {
-    const int sl = vsl[i];
-    const bool ok = static_cast<unsigned>(sl) < static_cast<unsigned>(a.num_slots);
-    vw[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(
-        vplane + (int64_t)(ok ? sl : 0) * a.row_bytes + head0 + vpiece * 16));
-  }
-
+  u32x4 kr[kLd], vr[kLd];
+  spread_slots(cur);
+  load_rows(kplane, kr);
+  load_rows(vplane, vr);
   __builtin_amdgcn_sched_barrier(0);
-  // ---- query operands (column `row` = head row % 8, scaled; its high part for row < 8, its
-  // low part for row >= 8): wave w builds chunks w, w + kWaves, ... for all 64 lanes into LDS
 #pragma unroll
-  for (int c = 0; c < kQC; ++c) {
-    const int ch = wave + c * kWaves;
+  for (int x = 0; x < kQC; ++x) {
+    const int ch = wave + x * kWaves;
     if (ch < kChunks) {
-      OpT qv8;
+      OpT part, rest;
 #pragma unroll
       for (int e = 0; e < kPer; ++e) {
-        const float q = real ? qraw[c][e] * a.scale : 0.f;
+        const float q = real ? qraw[x][e] * a.scale : 0.f;
         const ElemT hi = static_cast<ElemT>(q);
-        qv8[e] = low ? static_cast<ElemT>(q - static_cast<float>(hi)) : hi;
+        const float d = q - static_cast<float>(hi);
+        const ElemT lo = static_cast<ElemT>(d);
+        const ElemT third = static_cast<ElemT>(d - static_cast<float>(lo));
+        part[e] = low ? lo : hi;
+        if (kHeads == 4 && (row & 4) != 0) part[e] = low ? static_cast<ElemT>(0.f) : third;
+        rest[e] = low ? static_cast<ElemT>(0.f) : third;
       }
-      q_s[ch][lane] = qv8;
+      q_s[ch * kQ][lane] = part;
+      if constexpr (kQ == 2) q_s[ch * kQ + 1][lane] = rest;
     }
   }
+  __syncthreads();   // query operands in LDS; the K and V loads stay in flight
+  // this wave's window; only this wave touches it, and a wave's LDS operations run in order, so
+  // a compiler fence is all that its reads of other lanes' writes need
+  uint8_t* win = lds + wave * kWinB;
+  auto order_lds = [] { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); };
 
-  // ---- scores of this wave's tiles: lane holds tokens wt0 + 16i + 4*grp + j of head row % 8
-  // (columns row and row ^ 8 summed: lanes row and row + 8 then hold the same scores); the
-  // K/V loads above stay in flight across the barrier
-  __syncthreads();  // query operands in LDS
-  OpT qop[kChunks];
-#pragma unroll
-  for (int ch = 0; ch < kChunks; ++ch) qop[ch] = q_s[ch][lane];
-  f32x4 sc[kTiles];
-#pragma unroll
-  for (int i = 0; i < kTiles; ++i) {
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int ch = 0; ch < kChunks; ++ch) {
-      acc = score_mfma<kKind>(k_operand<kKind>(kw[i][ch]), qop[ch], acc);
-    }
-    // a slot outside the pool (its row was read at slot 0) poisons the request: NaN score;
-    // tokens past the split's end get weight zero
-    const uint64_t okm = __ballot(kok[i]);            // bit k: token k of the tile
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      acc[j] += row_ror<8>(acc[j]);
-      if (!((okm >> (4 * grp + j)) & 1)) acc[j] = __builtin_nanf("");
-      if (wt0 + 16 * i + 4 * grp + j >= nt) acc[j] = -INFINITY;
-    }
-    sc[i] = acc;
-  }
-
-  // ---- V rows of k-step kc into this wave's LDS window
-  uint8_t* vwin = lds + wave * kWin * kRowB;
-  auto stage_v = [&](int kc) {
-#pragma unroll
-    for (int ii = 0; ii < kItW; ++ii) {
-      const u32x4 w = vw[kc * kItW + ii];
-      uint8_t* dst = vwin + (lane / kLanesV + ii * kTokV) * kRowB + vpiece * kPerV * 2;
-      if constexpr (kKind == 2) {   // 16 fp8 values -> 16 bf16 values (32 bytes)
-        *reinterpret_cast<u32x4*>(dst) = v_row16<kKind>(u32x2{w.x, w.y});
-        *reinterpret_cast<u32x4*>(dst + 16) = v_row16<kKind>(u32x2{w.z, w.w});
-      } else {
-        *reinterpret_cast<u32x4*>(dst) = w;
-      }
-    }
-  };
-  stage_v(0);
-
-  // ---- wave-local softmax per head (the four lanes of a column share `row`)
-  float m = -INFINITY;
-#pragma unroll
-  for (int i = 0; i < kTiles; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) m = fmaxf(m, sc[i][j]);
-  m = lanes_reduce<16, true>(m);
-  const float msafe = m == -INFINITY ? 0.f : m;   // a wave with no valid token
-  float l = 0.f;
-#pragma unroll
-  for (int i = 0; i < kTiles; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      sc[i][j] = __expf(sc[i][j] - msafe);
-      l += sc[i][j];
-    }
-  l = lanes_reduce<16, false>(l);
-
-  // ---- O_w = P . V on the matrix cores, one 32-token k-step at a time; the V rows of a
-  // k-step go through this wave's LDS window (rows past the split's end weigh zero), the first
-  // k-step's before the softmax above
+  float m = -INFINITY, l = 0.f;
   f32x4 o[kDC];
 #pragma unroll
   for (int dc = 0; dc < kDC; ++dc) o[dc] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  auto round = [&](int i, auto more_t) {
+    constexpr bool kMore = decltype(more_t)::value;
+    // ---- K rows into the window; the next round's K loads
+    order_lds();
+    {
+      uint8_t* dst = win + (lane / kLanes) * kRowK + (lane % kLanes) * 16;
 #pragma unroll
-  for (int kc = 0; kc < kKC; ++kc) {
-    if (kc > 0) {
-      __syncthreads();  // the previous k-step's reads of the window are done
-      stage_v(kc);
+      for (int k = 0; k < kLd; ++k) *reinterpret_cast<u32x4*>(dst + k * kTok * kRowK) = kr[k];
     }
-    __syncthreads();  // V rows written (each wave reads only its own window)
-    // A operand: row `row` (head row % 8, high or low part), tokens 4*grp..+3 of tile 2kc
-    // then of tile 2kc+1 (zero if absent)
-    OpT pop;
+    order_lds();
+    if constexpr (kMore) {
+      spread_slots(nxt);
+      load_rows(kplane, kr);
+      nxt = load_slots(i + 2);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+
+    OpT qop[kChunks * kQ];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int tile = 2 * kc + (j >> 2);
-      const float p = tile < kTiles ? sc[tile < kTiles ? tile : 0][j & 3] : 0.f;
-      const ElemT hi = static_cast<ElemT>(p);
-      pop[j] = low ? static_cast<ElemT>(p - static_cast<float>(hi)) : hi;
-    }
-    // B operand rows: lane 16*grp + rho supplies the row of token 4*grp + rho/4 of the first
-    // tile (then of the second), elements 4*(rho%4)..+3 of the 16-element chunk
-    const int t1 = 4 * grp + row / 4;                                  // window rows
-    const int t2 = (2 * kc + 1 < kTiles ? 16 : 0) + 4 * grp + row / 4;
-    const uint8_t* r1 = vwin + t1 * kRowB + (row % 4) * 8;
-    const uint8_t* r2 = vwin + t2 * kRowB + (row % 4) * 8;
+    for (int ch = 0; ch < kChunks * kQ; ++ch) qop[ch] = q_s[ch][lane];
+    // ---- scores: lane holds tokens 16 t + 4*grp + j of its column's head (the columns of a
+    // head's parts summed: they then hold the same scores)
+    f32x4 sc[kTiles];
 #pragma unroll
-    for (int dc = 0; dc < kDC; ++dc) {
-      const i16x4 x1 = lds_read_tr16(r1 + dc * 32);
-      const i16x4 x2 = lds_read_tr16(r2 + dc * 32);
-      typedef short i16x8 __attribute__((ext_vector_type(8)));
-      const i16x8 xv = {x1[0], x1[1], x1[2], x1[3], x2[0], x2[1], x2[2], x2[3]};
-      const OpT vop = __builtin_bit_cast(OpT, xv);
-      o[dc] = score_mfma<kKind>(pop, vop, o[dc]);
+    for (int t = 0; t < kTiles; ++t) {
+      const uint8_t* src = win + (t * 16 + row) * kRowK;
+      // two chains of products
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f}, acc2 = {0.f, 0.f, 0.f, 0.f};
+      auto score = [&](OpT k, int ch) {
+        if constexpr (kQ == 2) {
+          acc = score_mfma<kKind>(k, qop[ch * kQ], acc);
+          acc2 = score_mfma<kKind>(k, qop[ch * kQ + kQ - 1], acc2);
+        } else if (ch % 2 == 0) {
+          acc = score_mfma<kKind>(k, qop[ch], acc);
+        } else {
+          acc2 = score_mfma<kKind>(k, qop[ch], acc2);
+        }
+      };
+      if constexpr (kPairK) {
+#pragma unroll
+        for (int ch = 0; ch < kChunks; ch += 2) {
+          const u32x4 w = *reinterpret_cast<const u32x4*>(src + ch * 32 + grp * 16);
+          score(k_operand<kKind>(u32x2{w.x, w.y}), ch);
+          score(k_operand<kKind>(u32x2{w.z, w.w}), ch + 1);
+        }
+      } else {
+#pragma unroll
+        for (int ch = 0; ch < kChunks; ++ch) {
+          const auto w = *reinterpret_cast<const typename Piece<kKind>::type*>(
+              src + (ch * 32 + grp * kPer) * kElem);
+          score(k_operand<kKind>(w), ch);
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        acc[j] += acc2[j];
+        acc[j] += row_ror<8>(acc[j]);
+        if (kHeads == 4) acc[j] += row_ror<4>(acc[j]);
+      }
+      sc[t] = acc;
     }
-  }
-  // result rows 4*grp + j: high parts in lane groups 0, 1 (heads 0-7), low parts 32 lanes up
+    const int left = nt - (wt0 + i * kStep);   // tokens of this round that exist
+    if (left < kIT) {   // (uniform) the last round of the request's last split
+#pragma unroll
+      for (int t = 0; t < kTiles; ++t)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          if (16 * t + 4 * grp + j >= left) sc[t][j] = -INFINITY;
+        }
+    }
+
+    // ---- softmax weights per head (the four lanes of a column share m)
+    float mi = sc[0][0];
+#pragma unroll
+    for (int t = 0; t < kTiles; ++t)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) mi = fmaxf(mi, sc[t][j]);
+    mi = fmaxf(m, lanes_reduce<16, true>(mi));
+    if (__ballot(mi != m) != 0) {
+      const float f = mi == m ? 1.f : __expf(m - mi);
+      m = mi;
+      l *= f;
+#pragma unroll
+      for (int dc = 0; dc < kDC; ++dc) o[dc] *= f;
+    }
+    const float msafe = m == -INFINITY ? 0.f : m;
+#pragma unroll
+    for (int t = 0; t < kTiles; ++t)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        sc[t][j] = __expf(sc[t][j] - msafe);
+        l += sc[t][j];
+      }
+
+    // ---- O2 += V^T . P2^T, one 32-token step at a time through the window
+#pragma unroll
+    for (int kc = 0; kc < kKC; ++kc) {
+      order_lds();
+#pragma unroll
+      for (int k = 0; k < kLdW; ++k) {
+        const u32x4 w = vr[kc * kLdW + k];
+        uint8_t* dst = win + (lane / kLanes + k * kTok) * kRowV + (lane % kLanes) * (32 / kElem);
+        if constexpr (kKind == 2) {   // 16 fp8 values -> 16 bf16 values (32 bytes)
+          *reinterpret_cast<u32x4*>(dst) = v_row16<kKind>(u32x2{w.x, w.y});
+          *reinterpret_cast<u32x4*>(dst + 16) = v_row16<kKind>(u32x2{w.z, w.w});
+        } else {
+          *reinterpret_cast<u32x4*>(dst) = w;
+        }
+      }
+      order_lds();
+      if constexpr (kMore) {
+        if (kc == kKC - 1) {   // V is in the window: the next round's loads
+          load_rows(vplane, vr);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      // P operand: column `row` (head row % 8, high or low part), tokens 4*grp..+3 of tile 2kc
+      // then of tile 2kc+1
+      ElemT pop[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int tile = 2 * kc + (j >> 2);
+        if (tile >= kTiles) continue;
+        const float p = sc[tile < kTiles ? tile : 0][j & 3];
+        const ElemT hi = static_cast<ElemT>(p);
+        pop[j] = low ? static_cast<ElemT>(p - static_cast<float>(hi)) : hi;
+      }
+      // V operand rows: lane 16*grp + rho supplies the row of token 4*grp + rho/4 of the first
+      // tile (then of the second), elements 4*(rho%4)..+3 of the 16-element chunk
+      const uint8_t* r1 = win + (4 * grp + row / 4) * kRowV + (row % 4) * 8;
+#pragma unroll
+      for (int dc = 0; dc < kDC; ++dc) {
+        const i16x4 x1 = lds_read_tr16(r1 + dc * 32);
+        if constexpr (kTiles > 1) {
+          const i16x4 x2 = lds_read_tr16(r1 + 16 * kRowV + dc * 32);
+          typedef short i16x8 __attribute__((ext_vector_type(8)));
+          const i16x8 xv = {x1[0], x1[1], x1[2], x1[3], x2[0], x2[1], x2[2], x2[3]};
+          const OpT pv = {pop[0], pop[1], pop[2], pop[3], pop[4], pop[5], pop[6], pop[7]};
+          o[dc] = score_mfma<kKind>(__builtin_bit_cast(OpT, xv), pv, o[dc]);
+        } else {
+          typedef ElemT ElemT4 __attribute__((ext_vector_type(4)));
+          const ElemT4 pv = {pop[0], pop[1], pop[2], pop[3]};
+          o[dc] = value_mfma4<kKind>(x1, __builtin_bit_cast(i16x4, pv), o[dc]);
+        }
+      }
+    }
+  };
+  for (int i = 0; i + 1 < rounds; ++i) round(i, std::true_type{});
+  if (rounds > 0) round(rounds - 1, std::false_type{});
+
+  // ---- merge the waves: [m, l] and O[head][d] per wave into LDS (element rows 4*grp + j of
+  // chunk dc: four consecutive values per lane)
+  l = lanes_reduce<16, false>(l);
+  if (__ballot(bad) != 0 && rounds > 0) l = __builtin_nanf("");
 #pragma unroll
   for (int dc = 0; dc < kDC; ++dc)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) o[dc][j] = xor_combine<32, false>(o[dc][j]);
-  __syncthreads();  // the LDS rows are reused for the merge
-
-  // ---- merge the waves: [m_w, l_w] and O_w[head][d] per wave into LDS
-  float* mrg = reinterpret_cast<float*>(lds);        // [wave][head][kD + 2]
-  if (grp == 0 && row < kG) {
-    mrg[(wave * kG + row) * (kD + 2)] = m;
-    mrg[(wave * kG + row) * (kD + 2) + 1] = l;
-  }
-  if (grp < 2) {
+    for (int j = 0; j < 4; ++j) o[dc][j] += row_ror<8>(o[dc][j]);
+  __syncthreads();  // the windows are reused for the merge
+  float* mrg = reinterpret_cast<float*>(lds);        // [wave][head][kRec]
+  if (row < G) {
+    float* rec = mrg + (wave * 8 + row) * kRec;
+    if (grp == 0) {
+      rec[0] = m;
+      rec[1] = l;
+    }
 #pragma unroll
-    for (int dc = 0; dc < kDC; ++dc)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int g = 4 * grp + j;                     // result row = head
-        if (g < kG) mrg[(wave * kG + g) * (kD + 2) + 2 + dc * 16 + row] = o[dc][j];
-      }
+    for (int dc = 0; dc < kDC; ++dc) {
+      *reinterpret_cast<f32x4*>(rec + 4 + dc * 16 + 4 * grp) = o[dc];
+    }
   }
   __syncthreads();
-  for (int i = tid; i < kG * kD; i += kThreads) {
-    const int g = i / kD, d = i - g * kD;
+  for (int i = tid; i < G * (kD / 4); i += kThreads) {
+    const int g = i / (kD / 4), d = i % (kD / 4) * 4;
     float M = -INFINITY;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) M = fmaxf(M, mrg[(w * kG + g) * (kD + 2)]);
-    float v = 0.f, L = 0.f;
+    for (int w = 0; w < kWaves; ++w) M = fmaxf(M, mrg[(w * 8 + g) * kRec]);
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    float L = 0.f;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
-      const float* wr = mrg + (w * kG + g) * (kD + 2);
+      const float* wr = mrg + (w * 8 + g) * kRec;
       const float f = wr[0] == -INFINITY ? 0.f : __expf(wr[0] - M);
-      v += wr[2 + d] * f;
+      v += *reinterpret_cast<const f32x4*>(wr + 4 + d) * f;
       L += wr[1] * f;
     }
-    float* rec = a.workspace +
-                 (((int64_t)r * a.num_q_heads + h * kG + g) * a.splits + split) * (kD + 2);
-    rec[2 + d] = v;
+    if (a.splits == 1) {
+      *reinterpret_cast<f32x4*>(a.out + (qh0 + g) * kD + d) = v * (1.f / L);
+      continue;
+    }
+    float* rec = a.workspace + ((qh0 + g) * a.splits + split) * (kD + 2);
+    rec[2 + d] = v.x;
+    rec[3 + d] = v.y;
+    rec[4 + d] = v.z;
+    rec[5 + d] = v.w;
     if (d == 0) {
       rec[0] = M;
       rec[1] = L;
@@ -616,170 +726,132 @@ void decode_split_kernel(AttnArgs a) {
 }
 
 // Merge of the split partials of one (request, query head): M = max of the split maxima,
-// weights w_s = exp(m_s - M), out = sum_s w_s acc_s / sum_s w_s l_s. The splits are spread
-// over the threads (maxima, weights) and the head elements over the threads (weighted sum,
-// 128 splits per chunk with their weights in LDS), so no thread walks the splits alone.
-// Each thread reads the (m_s, l_s) pair of its first split once, and the values of the first
-// kCombinePre splits are loaded before the two reductions, so that the call waits for about
-// two dependent rounds of loads instead of four; the remaining splits go 8, then 4 at a time.
-constexpr int kCombineThreads = 128;
-constexpr int kCombinePre = 8;
+// weights w_s = exp(m_s - M), out = sum_s w_s acc_s / sum_s w_s l_s. Bound: latency (a merge
+// reads ns records of kD + 2 floats). Every wave reads all the (m_s, l_s) pairs, 64 at a time, and
+// so knows M, the weights and the divisor without a barrier; the records are shared out over the
+// waves, a whole one per load, and the first kCombinePre of each wave are read before anything
+// else is known. The waves' sums meet in LDS once. With all threads on every record, eight at a
+// time, 282 records of 128 took 17 us, with 16 waves so 4.5.
+constexpr int kCombinePre = 4;
+constexpr int kCombineWaves = 4;
+constexpr int kCombineWavesMany = 16;
+constexpr int kCombineManySplits = 32;   // more splits: 16 waves
 
-template <bool kMax>
-__device__ __forceinline__ float block_reduce(float v, float* red) {
-  v = lanes_reduce<1, kMax>(v);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  v = red[0];
-#pragma unroll
-  for (int w = 1; w < kCombineThreads / 64; ++w) v = kMax ? fmaxf(v, red[w]) : v + red[w];
-  __syncthreads();
-  return v;
-}
-
-__global__ __launch_bounds__(kCombineThreads) void decode_combine_kernel(AttnArgs a) {
-  __shared__ float red[kCombineThreads / 64];
-  __shared__ float w_s[kCombineThreads];
+template <int kWaves>
+__global__ __launch_bounds__(64 * kWaves) void decode_combine_kernel(AttnArgs a) {
+  constexpr int kMaxD = 256;
+  __shared__ float sum_s[kWaves][kMaxD];
   const int qh = blockIdx.x % a.num_q_heads;
   const int r = blockIdx.x / a.num_q_heads;
   if (r >= a.num_reqs) return;
   const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int s0 = a.slot_indptr[r];
   const int c = a.slot_count != nullptr ? a.slot_count[r] : a.slot_indptr[r + 1] - s0;
   const int D = a.head_dim;
   const int64_t rs = D + 2;  // record stride
   float* out = a.out + ((int64_t)r * a.num_q_heads + qh) * D;
-  const int ns = c <= 0 ? 0 : (c + a.split_tokens - 1) / a.split_tokens;
-  // a malformed slot range (the split kernel computed nothing for it), or more slots than
-  // max_tokens (the splits past the workspace were never computed): NaN
-  if (s0 < 0 || c < 0 || ns > a.splits) {
-    for (int d = tid; d < D; d += kCombineThreads) out[d] = __builtin_nanf("");
+  if (decode_fixed_output(a, s0, c)) {
+    const float fill = c == 0 && s0 >= 0 ? 0.f : __builtin_nanf("");
+    for (int d = tid; d < D; d += 64 * kWaves) out[d] = fill;
     return;
   }
-  if (ns == 0) {
-    for (int d = tid; d < D; d += kCombineThreads) out[d] = 0.f;
-    return;
-  }
+  const int ns = min(static_cast<int>(((int64_t)c + a.split_tokens - 1) / a.split_tokens), a.splits);
   const float* rec0 = a.workspace + ((int64_t)r * a.num_q_heads + qh) * a.splits * rs;
-  // each thread owns head elements d = tid, tid + 128 (head_dim <= 256)
-  const int d0 = tid, d1 = tid + kCombineThreads;
-  float p0[kCombinePre], p1[kCombinePre];
+  // A record's values: float pairs (its start and its stride are even), pair lane and lane + 64
+  const int p0 = lane * 2, p1 = 128 + lane * 2;
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  auto pair = [&](int s, int p) {
+    return s < ns && p < D ? *reinterpret_cast<const f32x2*>(rec0 + s * rs + 2 + p)
+                           : f32x2{0.f, 0.f};
+  };
+  f32x2 x0[kCombinePre], x1[kCombinePre];
 #pragma unroll
   for (int j = 0; j < kCombinePre; ++j) {
-    p0[j] = j < ns && d0 < D ? rec0[j * rs + 2 + d0] : 0.f;
-    p1[j] = j < ns && d1 < D ? rec0[j * rs + 2 + d1] : 0.f;
+    x0[j] = pair(wave + j * kWaves, p0);
+    x1[j] = pair(wave + j * kWaves, p1);
   }
-  // (m_s, l_s) of split s = tid, both issued before either is used
-  float m0 = -INFINITY, l0 = 0.f;
-  if (tid < ns) {
-    m0 = rec0[tid * rs];
-    l0 = rec0[tid * rs + 1];
-  }
-  float m = m0;
-  for (int s = tid + kCombineThreads; s < ns; s += kCombineThreads) m = fmaxf(m, rec0[s * rs]);
-  const float M = block_reduce<true>(m, red);
-  const float w0 = tid < ns ? __expf(m0 - M) : 0.f;
-  float l = tid < ns ? l0 * w0 : 0.f;
-  for (int s = tid + kCombineThreads; s < ns; s += kCombineThreads) {
-    l += rec0[s * rs + 1] * __expf(rec0[s * rs] - M);
-  }
-  const float L = block_reduce<false>(l, red);
-  const float inv = 1.f / L;
-  float v0 = 0.f, v1 = 0.f;
-  for (int base = 0; base < ns; base += kCombineThreads) {
-    const int n = ns - base < kCombineThreads ? ns - base : kCombineThreads;
-    if (tid < n) w_s[tid] = base == 0 ? w0 : __expf(rec0[(base + tid) * rs] - M);
-    __syncthreads();
-    const float* rb = rec0 + (int64_t)base * rs + 2;
-    int j = 0;
+  auto head_of = [&](int s) {   // (m_s, l_s)
+    return s < ns ? *reinterpret_cast<const f32x2*>(rec0 + s * rs) : f32x2{-INFINITY, 0.f};
+  };
+  const f32x2 first = head_of(lane);
+  float M = first.x;
+  for (int s = lane + 64; s < ns; s += 64) M = fmaxf(M, rec0[s * rs]);
+  M = lanes_reduce<1, true>(M);
+  float L = 0.f;
+  f32x2 v0 = {0.f, 0.f}, v1 = {0.f, 0.f};
+  for (int base = 0; base < ns; base += 64) {
+    const f32x2 ml = base == 0 ? first : head_of(base + lane);
+    const float wt = base + lane < ns ? __expf(ml.x - M) : 0.f;
+    L += ml.y * wt;
+    auto weight = [&](int s) {   // of split base + s; zero past the last
+      return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wt), s));
+    };
+    int s = wave;
     if (base == 0) {
 #pragma unroll
-      for (int i = 0; i < kCombinePre; ++i) {
-        if (i < n) {
-          v0 += p0[i] * w_s[i];
-          v1 += p1[i] * w_s[i];
-        }
+      for (int j = 0; j < kCombinePre; ++j) {
+        const float w = weight(wave + j * kWaves);
+        v0 += x0[j] * w;
+        v1 += x1[j] * w;
       }
-      j = n < kCombinePre ? n : kCombinePre;
+      s += kCombinePre * kWaves;
     }
-    for (; j + 8 <= n; j += 8) {
-      if (d0 < D) {
-        float x[8];
+    for (; s < 64 && base + s < ns; s += 4 * kWaves) {
+      f32x2 y0[4], y1[4];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) x[u] = rb[(j + u) * rs + d0];
+      for (int j = 0; j < 4; ++j) {
+        const int t = s + j * kWaves < 64 ? base + s + j * kWaves : ns;
+        y0[j] = pair(t, p0);
+        y1[j] = pair(t, p1);
+      }
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v0 += x[u] * w_s[j + u];
+      for (int j = 0; j < 4; ++j) {
+        const float w = s + j * kWaves < 64 ? weight(s + j * kWaves) : 0.f;
+        v0 += y0[j] * w;
+        v1 += y1[j] * w;
       }
-      if (d1 < D) {
-        float x[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) x[u] = rb[(j + u) * rs + d1];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v1 += x[u] * w_s[j + u];
-      }
-    }
-    for (; j + 4 <= n; j += 4) {
-      if (d0 < D) {
-        v0 += rb[j * rs + d0] * w_s[j] + rb[(j + 1) * rs + d0] * w_s[j + 1] +
-              rb[(j + 2) * rs + d0] * w_s[j + 2] + rb[(j + 3) * rs + d0] * w_s[j + 3];
-      }
-      if (d1 < D) {
-        v1 += rb[j * rs + d1] * w_s[j] + rb[(j + 1) * rs + d1] * w_s[j + 1] +
-              rb[(j + 2) * rs + d1] * w_s[j + 2] + rb[(j + 3) * rs + d1] * w_s[j + 3];
-      }
-    }
-    for (; j < n; ++j) {
-      if (d0 < D) v0 += rb[j * rs + d0] * w_s[j];
-      if (d1 < D) v1 += rb[j * rs + d1] * w_s[j];
-    }
-    __syncthreads();
-  }
-  if (d0 < D) out[d0] = v0 * inv;
-  if (d1 < D) out[d1] = v1 * inv;
-}
-
-template <int kKind, int kD, int kG, int kWaves>
-hipError_t launch_split_w(const AttnArgs& a, hipStream_t stream) {
-  const dim3 grid(
-      static_cast<unsigned>((int64_t)a.num_reqs * a.num_kv_heads * decode_grid_splits(a.splits)));
-  auto kernel = decode_split_kernel<kKind, kD, kG, kWaves>;
-  hipLaunchKernelGGL(kernel, grid, dim3(64 * kWaves), 0, stream, a);
-  return hipGetLastError();
-}
-
-// the split size the host chose (decode_waves_for) selects the workgroup's waves
-template <int kKind, int kD, int kG>
-hipError_t launch_split(const AttnArgs& a, hipStream_t stream) {
-  constexpr int kElem = kKind == 2 ? 1 : 2;
-  constexpr int kBase = decode_split_waves(kElem, kG);
-  if constexpr (kElem == 2 && kBase == 4) {
-    if (a.split_tokens == decode_split_tokens_w(kD, kElem, 8)) {
-      return launch_split_w<kKind, kD, kG, 8>(a, stream);
     }
   }
-  return launch_split_w<kKind, kD, kG, kBase>(a, stream);
+  L = lanes_reduce<1, false>(L);
+  static_assert(kCombinePre * kCombineWavesMany <= 64, "the first records have weights in a lane");
+  if (p0 < D) *reinterpret_cast<f32x2*>(&sum_s[wave][p0]) = v0;
+  if (p1 < D) *reinterpret_cast<f32x2*>(&sum_s[wave][p1]) = v1;
+  __syncthreads();
+  const float inv = 1.f / L;
+  for (int d = tid; d < D; d += 64 * kWaves) {
+    float v = 0.f;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) v += sum_s[w][d];
+    out[d] = v * inv;
+  }
 }
 
 template <int kKind, int kD>
-hipError_t launch_decode_g(const AttnArgs& a, hipStream_t stream) {
-  switch (a.num_q_heads / a.num_kv_heads) {
-    case 1: return launch_split<kKind, kD, 1>(a, stream);
-    case 2: return launch_split<kKind, kD, 2>(a, stream);
-    case 4: return launch_split<kKind, kD, 4>(a, stream);
-    case 8: return launch_split<kKind, kD, 8>(a, stream);
-    default: return hipErrorInvalidValue;
+auto split_kernel(bool g8) -> void (*)(AttnArgs) {
+  if constexpr (kKind == 0) {
+    return decode_split_kernel<kKind, kD, false>;   // one kernel for all groups
+  } else {
+    return g8 ? decode_split_kernel<kKind, kD, true> : decode_split_kernel<kKind, kD, false>;
   }
 }
 
 template <int kKind>
-hipError_t launch_decode_k(const AttnArgs& a, hipStream_t stream) {
+hipError_t launch_split(const AttnArgs& a, hipStream_t stream) {
+  const int64_t groups = decode_grid_groups((int64_t)a.num_reqs * decode_grid_splits(a.splits));
+  const dim3 grid(static_cast<unsigned>(groups * a.num_kv_heads));
+  const bool g8 = kKind != 0 && a.num_q_heads == 8 * a.num_kv_heads;
+  void (*kernel)(AttnArgs) = nullptr;
   switch (a.head_dim) {
-    case 32: return launch_decode_g<kKind, 32>(a, stream);
-    case 64: return launch_decode_g<kKind, 64>(a, stream);
-    case 128: return launch_decode_g<kKind, 128>(a, stream);
-    case 256: return launch_decode_g<kKind, 256>(a, stream);
+    case 32: kernel = split_kernel<kKind, 32>(g8); break;
+    case 64: kernel = split_kernel<kKind, 64>(g8); break;
+    case 128: kernel = split_kernel<kKind, 128>(g8); break;
+    case 256: kernel = split_kernel<kKind, 256>(g8); break;
     default: return hipErrorInvalidValue;
   }
+  hipLaunchKernelGGL(kernel, grid, dim3(64 * kSplitWaves), 0, stream, a);
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -802,23 +874,24 @@ hipError_t launch_slot_mapping(const SlotMapArgs& a, hipStream_t stream) {
 
 hipError_t launch_paged_decode(const AttnArgs& a, hipStream_t stream) {
   if (a.num_reqs <= 0) return hipSuccess;
-  const int elem = a.kv_kind == 2 ? 1 : 2;
-  const int group = a.num_q_heads / a.num_kv_heads;
-  if (a.split_tokens != decode_split_tokens(a.head_dim, elem, group) &&
-      (elem != 2 || a.split_tokens != decode_split_tokens_w(a.head_dim, elem, 8))) {
-    return hipErrorInvalidValue;
-  }
+  const int round = decode_round_tokens(a.head_dim, a.kv_kind == 2 ? 1 : 2);
+  if (a.split_tokens <= 0 || a.split_tokens % round != 0) return hipErrorInvalidValue;
   hipError_t e;
   switch (a.kv_kind) {
-    case 0: e = launch_decode_k<0>(a, stream); break;
-    case 1: e = launch_decode_k<1>(a, stream); break;
-    case 2: e = launch_decode_k<2>(a, stream); break;
+    case 0: e = launch_split<0>(a, stream); break;
+    case 1: e = launch_split<1>(a, stream); break;
+    case 2: e = launch_split<2>(a, stream); break;
     default: return hipErrorInvalidValue;
   }
+  // a single split has written the outputs
+  if (a.splits == 1) return e;
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(decode_combine_kernel, dim3(static_cast<unsigned>(
-                         (int64_t)a.num_reqs * a.num_q_heads)), dim3(kCombineThreads), 0,
-                     stream, a);
+  const bool many = a.splits > kCombineManySplits;
+  const int waves = many ? kCombineWavesMany : kCombineWaves;
+  hipLaunchKernelGGL(many ? decode_combine_kernel<kCombineWavesMany>
+                          : decode_combine_kernel<kCombineWaves>,
+                     dim3(static_cast<unsigned>((int64_t)a.num_reqs * a.num_q_heads)),
+                     dim3(64 * waves), 0, stream, a);
   return hipGetLastError();
 }
 

@@ -186,7 +186,8 @@ struct AttnArgs {
   int32_t num_slots;
   int32_t num_reqs;
   int32_t splits;    // split records per (request, query head) in the workspace
-  int32_t split_tokens;  // tokens per split: decode_split_tokens_w(head_dim, elem bytes, waves)
+  int32_t split_tokens;  // tokens per split: a multiple of decode_round_tokens()
+  int64_t max_count;     // slots a request may hold (more: NaN outputs)
   float scale;
   const float* q;
   float* out;
@@ -248,42 +249,60 @@ hipError_t launch_paged_decode(const AttnArgs& a, hipStream_t stream);
 // on the device of `stream` (looked up on the first call per device; allocates nothing).
 constexpr int64_t kDecodeScratchBytes = VTOKEN_DECODE_SCRATCH_BYTES;
 hipError_t decode_scratch(hipStream_t stream, float** out);
-// Decode split geometry. Each wave of a split workgroup covers 8 KiB of K (and of V) of one
-// KV head: 128 bytes per lane and operand. A workgroup has 4 waves, or 8 for 16-bit caches
-// with GQA groups of 8, whose per-workgroup work (query operands, the merge of the waves, a
-// split record of 8 heads) is then spread over twice the tokens (measured +11%; 8 waves were
-// slower for fp8, whose waves already cover twice the tokens). 16-bit caches at smaller
-// groups take 8 waves too when the batch's longest request spans kDecodeLongSplits 4-wave
-// splits or more (half the split records: Llama-3-70B bf16, requests of 16-64K tokens, G = 1,
-// 2, 4 faster by 4.8%, 4.4%, 2.8%; on the Llama-3-8B batches, ~27 splits, 8 waves were 0-4%
-// slower: fewer, longer workgroups leave a longer tail).
-constexpr int kDecodeWaveBytes = 8192;
-constexpr int kDecodeLongSplits = 64;
-constexpr int decode_split_waves(int elem_bytes, int group) {
-  return elem_bytes == 2 && group == 8 ? 8 : 4;
+// Decode split geometry. In a round each of a split workgroup's four waves takes 4 KiB of K (and
+// of V) of one KV head, 64 bytes per lane and operand, but at least a tile of 16 tokens.
+constexpr int kDecodeSplitWaves = 4;
+constexpr int decode_wave_tokens(int head_dim, int elem_bytes) {
+  return head_dim * elem_bytes > 256 ? 16 : 4096 / (head_dim * elem_bytes);
 }
-// Tokens one split workgroup of `waves` waves covers (head_dim 32, 64, 128, 256 -> 512, 256,
-// 128, 64 tokens for 16-bit caches with 4 waves; twice as many with 8 waves or at 1 byte per
-// element).
-constexpr int decode_split_tokens_w(int head_dim, int elem_bytes, int waves) {
-  return waves * kDecodeWaveBytes / (head_dim * elem_bytes);
+constexpr int decode_round_tokens(int head_dim, int elem_bytes) {
+  return kDecodeSplitWaves * decode_wave_tokens(head_dim, elem_bytes);
 }
-constexpr int decode_split_tokens(int head_dim, int elem_bytes, int group) {
-  return decode_split_tokens_w(head_dim, elem_bytes, decode_split_waves(elem_bytes, group));
+// A split is 1, 2, 4 or 8 units of 32 KiB of K (whole rounds; head_dim 32, 64, 128, 256 -> 512,
+// 256, 128, 64 tokens a unit for 16-bit caches, twice as many at 1 byte per element).
+constexpr int decode_unit_tokens(int head_dim, int elem_bytes) {
+  return 32768 / (head_dim * elem_bytes);
 }
-// Waves per split workgroup for a batch whose requests hold at most max_tokens slots.
-constexpr int decode_waves_for(int head_dim, int elem_bytes, int group, int64_t max_tokens) {
-  return elem_bytes == 2 && decode_split_waves(elem_bytes, group) == 4 &&
-                 max_tokens >= (int64_t)kDecodeLongSplits *
-                                   decode_split_tokens_w(head_dim, elem_bytes, 4)
-             ? 8
-             : decode_split_waves(elem_bytes, group);
+// Units per split for `pairs` (request, KV head) pairs of at most max_tokens slots. Short splits
+// pay the start of a workgroup (3 dependent reads, the query operands) and its record often, long
+// ones leave the chip part idle at the end: the time is estimated as the workgroups' rounds
+// through the chip plus half a workgroup's time, with a start of 3 us and a unit's 64 KiB of K
+// and V at the workgroup's share of 7 TB/s (resident workgroups: 3 per CU, 2 with 512-byte head
+// rows). Measured per layer for 1, 2, 4, 8 units (estimate's choice in brackets): bf16, 64
+// requests of 678-2,521 slots, 8 heads x 128 86, 79.5, [78], 83 us; fp8, 29 of 5-20K 164, 149,
+// [143], 144; fp8, 45 of 1.4-2.6K [37.4], 37.4, 39, 53; bf16, 18 of 6K, 4 x 256 107, 89, [83],
+// 80; bf16, 5 of 1.0-1.6K, 8 x 256 23.4, [19.1], 20.7, 19.4.
+constexpr int decode_split_units(int head_dim, int elem_bytes, int64_t pairs,
+                                 int64_t max_tokens) {
+  const int resident = 256 * (head_dim * elem_bytes > 256 ? 2 : 3);
+  const double start = 3.0, unit = 65536.0 * resident / 7e6;   // us
+  const int64_t tokens = decode_unit_tokens(head_dim, elem_bytes);
+  int best = 1;
+  double best_time = 0;
+  for (int u = 1; u <= 8; u *= 2) {
+    const double one = start + u * unit;
+    const double groups = static_cast<double>(pairs) *
+                          static_cast<double>((max_tokens + u * tokens - 1) / (u * tokens));
+    const double time = groups * one / resident + one / 2;
+    if (u == 1 || time < best_time) {
+      best = u;
+      best_time = time;
+    }
+  }
+  return best;
 }
-// The smallest split over the element sizes and groups: the workspace bound of the C ABI.
-constexpr int decode_min_split_tokens(int head_dim) {
-  return decode_split_tokens(head_dim, 2, 1);
+// The most slots a request may hold: max_tokens rounded up to whole units of the size below (at
+// least one), which is what the C ABI has promised since splits had that size.
+constexpr int64_t decode_max_count(int head_dim, int elem_bytes, int group, int64_t max_tokens) {
+  const int64_t base = decode_unit_tokens(head_dim, elem_bytes);
+  const bool twice = elem_bytes == 2 && (group == 8 || max_tokens >= 64 * base);
+  const int64_t unit = twice ? 2 * base : base;
+  return max_tokens > 0 ? (max_tokens + unit - 1) / unit * unit : unit;
 }
-// Split slots per (request, KV head) in the split launch's grid. Workgroups are handed to the
+// The smallest split over the element sizes: the workspace bound of the C ABI.
+constexpr int decode_min_split_tokens(int head_dim) { return decode_unit_tokens(head_dim, 2); }
+// Split slots per (request, KV head) in the split launch's grid (where the splits of a head are
+// neighbours). Workgroups are handed to the
 // 8 XCDs in turn, so with an even count and few splits the requests' first splits, which hold
 // the work, fall on the same XCDs (Llama-3-8B Random, 20 splits: one XCD 12% above the mean);
 // rounding a count below 64 up to an odd one spreads them evenly (measured: that call 5%
@@ -292,6 +311,10 @@ constexpr int decode_min_split_tokens(int head_dim) {
 __host__ __device__ constexpr int decode_grid_splits(int splits) {
   return splits < 64 ? (splits | 1) : splits;
 }
+
+// (request, split) pairs of the split launch's grid: whole octets, for the kernels that place the
+// heads of a split on one XCD.
+__host__ __device__ constexpr int64_t decode_grid_groups(int64_t n) { return (n + 7) / 8 * 8; }
 
 hipError_t launch_build(const MetaArgs& a, hipStream_t stream);
 // variant: 0 default, 1 LDS double buffer, 2 LDS single buffer, 3 registers
