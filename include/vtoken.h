@@ -223,10 +223,10 @@ vtoken_status vtoken_check_layout(const vtoken_cache* cache, const vtoken_batch*
  * hold src_plan_capacity >= M*S. Call order: vtoken_build_token_table_inplace, then
  * vtoken_repack_inplace, then vtoken_free_blocks (the freed list is the released tails).
  * vtoken_repack_inplace requires block_size*row_bytes <= 64 KiB (VTOKEN_ERR_SHAPE otherwise):
- * one workgroup walks each (request, plane) chain in block order and holds one destination
- * block's moving rows at a time (in registers by default; in LDS with the staging variants of
- * vtoken_repack_inplace_ex), so that a block is written only after every read of its own and
- * earlier destination blocks. Handed a plan of vtoken_build_token_table, it copies nothing and
+ * one wave walks each column slice of a (request, plane) chain in row order, holding two groups
+ * of moving rows at a time (the staging variants of vtoken_repack_inplace_ex: one workgroup
+ * walks the whole (request, plane) chain a destination block at a time), so that a row is
+ * written only after every read for it and the rows before it. Handed a plan of vtoken_build_token_table, it copies nothing and
  * sets counters[3] to VTOKEN_ERR_PLAN_MODE (and vtoken_repack does the same with an in-place
  * plan). */
 vtoken_status vtoken_build_token_table_inplace(const vtoken_cache* cache,
@@ -263,13 +263,12 @@ vtoken_status vtoken_repack_ex(const vtoken_cache* cache, const vtoken_batch* ba
                                hipStream_t stream);
 
 /* Tuning entry for the in-place copy; vtoken_repack_inplace uses the default (variant 0).
- *   variant: how a destination block is staged between its reads and its writes:
- *            0 default (4 for block_size <= 64, else 3), 1 LDS double buffer (direct
- *            global->LDS loads; falls back to
- *            2 when two blocks exceed 64 KiB), 2 LDS single buffer, 3 registers, 4 registers
- *            with the next moving block's reads in flight while a block is written
- *            (block_size <= 64; larger blocks use 3)
- *   grid, order: must be 0 (one workgroup per (request, plane) chain)
+ *   variant: how rows are staged between their reads and their writes:
+ *            0 default (= 4), 1 a destination block in LDS, double buffer (direct global->LDS
+ *            loads; falls back to 2 when two blocks exceed 64 KiB), 2 a block in LDS, single
+ *            buffer, 3 a block in registers, 4 groups of moving rows in registers, one wave per
+ *            column slice, the next group's reads in flight while a group is written
+ *   grid, order: must be 0
  * All variants produce identical bytes. */
 vtoken_status vtoken_repack_inplace_ex(const vtoken_cache* cache, const vtoken_batch* batch,
                                        const vtoken_plan* plan,

@@ -4,11 +4,15 @@
 //   repack_direct_kernel        the out-of-place gather-repack (Sec. 3.3, 3.3.4): every live
 //                               K/V row of every admitted request into packed destination
 //                               blocks, all layers, K and V, all KV heads in one launch
-//   repack_inplace_kernel,      in-place compaction: one workgroup walks each (request, plane)
-//   repack_inplace_pipe_kernel  chain in block order (the hazard rule below)
+//   repack_inplace_rows_kernel  in-place compaction: one wave walks each (request, plane, column
+//                               slice) chain in row order (the hazard rule below)
+//   repack_inplace_kernel       its staging variants: one workgroup walks each (request, plane)
+//                               chain in block order
 //
 // Both read the status word plan->counters[3] and do nothing when it is set, and check the
 // plan's mode word plan->counters[4]. No MFMA, no arithmetic on the payload: byte movement.
+#include <type_traits>
+
 #include "vtoken_internal.h"
 
 namespace vtoken {
@@ -494,30 +498,44 @@ constexpr int vmcnt_imm(int n) {
   return (n & 0xF) | (((n >> 4) & 3) << 14) | (0x7 << 4) | (0xF << 8);
 }
 
-// Pipelined in-place copy (S <= 64): the reads of the next moving block are in flight while
-// the current block is written. Vector-memory counters retire in order, so a wait for a
-// block's reads is only cheap when nothing after them is waited for too: the plan rows and
-// destination blocks of 32 blocks at a time are staged in LDS first (one drain per 32 blocks),
-// the blocks whose rows move are listed there, and the listed blocks are walked with exactly
-// kV reads and kV writes per thread each, so every wait count is static: a unit that does not
-// move (a row already in place inside a moving block, a padding row, past the block) reads
-// the plane's first 16 bytes (one cached line) and its store goes to a dropped buffer offset.
-// Hazards: the sources of destination block b lie at table positions >= b, so the reads of a
-// later listed block never touch the block being written; a block is written only after the
-// barrier that every thread reaches once its own reads of that block have returned, and the
-// reads of earlier blocks that touched it returned before earlier barriers. Blocks left out
-// of the list have all their rows in place: nothing reads from them for another block.
+// Row walk of the in-place copy (the default): the chain of a (request, plane) is cut into
+// column slices of at most 64 16-byte units, and every slice is a chain of its own, walked by
+// one wave with no barrier inside. The workgroup stages the moves of some thousand destination
+// rows in LDS at a time (source slot, destination slot; rows already in place, padding rows and
+// rows of an invalid block are left out), and each of its waves walks them for its own slice in
+// groups of kV instructions, the reads of the next group in flight while a group is written.
+// Hazards: in logical order the positions q_k of the moves' destinations increase, and a row's
+// source position p_k is larger than q_k. A move's destination can be the source of earlier
+// moves only (p_j = q_k gives q_j < q_k), so a group is written once its own reads and those of
+// the groups before have returned; and no later read lies at an earlier destination
+// (p_j > q_j > q_k). Slices touch other bytes.
+//
+// Bound: HBM where there are thousands of chains, else what one compute unit gets out of rows
+// far apart (16 KiB in flight per wave instead of 8 change nothing, the same waves on four times
+// the compute units nearly double the rate). So a launch of fewer than kInplaceFewChains
+// chains has workgroups of one wave (kFew). Whole passes, before (one workgroup per (request,
+// plane), a block at a time) and with workgroups of four waves and of one: fp8, 13 requests of
+// 100K tokens, 1 layer x 8 heads x 128 (208 chains) 3,361, 1,631 and 951 us; bf16, 2 of 80K,
+// 4 layers x 2 x 64 (32) 657, 355, 219; bf16, 6 of 72K, 32 x 2 x 64 (768) 4,627, 2,060, 1,935;
+// Llama-3-8B, 4 of 2-8K (4,096) 368, 337, 394. Non-temporal stores gain where HBM bounds
+// (Llama-3-70B at TP 8, 16 of 16-64K, H2O: 977 us with plain stores, 929 so) and lose with few
+// chains (2 of 43K, 32 x 1 x 128, 256 chains: 158 us plain, 167 so).
 constexpr int kLongestFirstMaxReqs = 256;
+constexpr int kInplaceGroup = 8;                          // instructions of a group
 
-template <int kV>
-__global__ __launch_bounds__(kCopyThreads) void repack_inplace_pipe_kernel(InplaceArgs a) {
-  constexpr int kChunkBlocks = 32;
-  constexpr int kWaves = kCopyThreads / 64;
-  __shared__ int plan_s[kChunkBlocks * 64];
-  __shared__ int dblk_s[kChunkBlocks];
-  __shared__ int flag_s[kChunkBlocks];
-  __shared__ int list_s[kChunkBlocks];
-  __shared__ int nlist_s;
+template <int kV, int kWsh, bool kFew>
+__global__ __launch_bounds__(kFew ? 64 : kCopyThreads)
+__attribute__((amdgpu_waves_per_eu(kFew ? 2 : 4)))
+void repack_inplace_rows_kernel(InplaceArgs a, int slices, int64_t items) {
+  constexpr int kThreads = kFew ? 64 : kCopyThreads;
+  constexpr int kWaves = kThreads / 64;
+  constexpr int kMoveTile = kFew ? 16 : 8;             // rows a thread stages
+  constexpr int kMoveRows = kThreads * kMoveTile;      // destination rows staged at a time
+  constexpr int kRows = 64 >> kWsh;                    // rows of an instruction
+  constexpr int kGroup = kV * kRows;                   // rows of a group
+  __shared__ int2 move_s[kMoveRows + 2 * kGroup];
+  __shared__ int wave_tot[kWaves];
+  __shared__ int need_s[kLongestFirstMaxReqs];
   __shared__ int r_s;
   if (a.counters[3] != 0) return;
   if (a.counters[4] != kPlanInPlace) {
@@ -525,22 +543,30 @@ __global__ __launch_bounds__(kCopyThreads) void repack_inplace_pipe_kernel(Inpla
     return;
   }
   if (a.counters[1] == 0) return;   // nothing admitted
-  const int P = a.num_planes;
-  // longest chains first: workgroup k*P + plane takes the request with the k-th longest
+  const int S = a.block_size;
+  const int tid = static_cast<int>(threadIdx.x);
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t chains = (int64_t)a.num_planes * slices;
+  const int64_t per_req = (chains + kWaves - 1) / kWaves;   // workgroups of a request
+  const int64_t w = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+  if (w >= items) return;
+  // longest chains first: workgroups k * per_req .. take the request with the k-th longest
   // chain (ties by index), so the last workgroups to start are short ones and the tail of the
-  // launch is short; the ranking costs O(R) per thread, so it is done for R <= 256 only
-  const int k = static_cast<int>(blockIdx.x / P);
-  const int plane = static_cast<int>(blockIdx.x - (int64_t)k * P);
-  if (k >= a.num_reqs) return;
+  // launch is short; for R <= 256 only (every workgroup ranks the requests)
+  const int k = static_cast<int>(w / per_req);
+  const int64_t chain = (w - (int64_t)k * per_req) * kWaves + wave;
   int r = k;
   if (a.num_reqs <= kLongestFirstMaxReqs) {
-    if (threadIdx.x == 0) r_s = k;
+    for (int i = tid; i < a.num_reqs; i += kThreads) {
+      need_s[i] = a.admitted[i] ? a.dst_indptr[i + 1] - a.dst_indptr[i] : 0;
+    }
     __syncthreads();
-    for (int i = threadIdx.x; i < a.num_reqs; i += kCopyThreads) {
-      const int ni = a.admitted[i] ? a.dst_indptr[i + 1] - a.dst_indptr[i] : 0;
+    for (int i = tid; i < a.num_reqs; i += kThreads) {
+      const int ni = need_s[i];
       int rank = 0;
       for (int j = 0; j < a.num_reqs; ++j) {
-        const int nj = a.admitted[j] ? a.dst_indptr[j + 1] - a.dst_indptr[j] : 0;
+        const int nj = need_s[j];
         rank += (nj > ni) || (nj == ni && j < i);
       }
       if (rank == k) r_s = i;
@@ -552,122 +578,203 @@ __global__ __launch_bounds__(kCopyThreads) void repack_inplace_pipe_kernel(Inpla
   const int g0 = a.dst_indptr[r];
   const int need = a.dst_indptr[r + 1] - g0;
   const int nb0 = a.new_bt_indptr[r];
-  const int S = a.block_size;
-  if (g0 < 0 || need <= 0 || nb0 < 0 || (int64_t)(g0 + need) * S > a.src_plan_capacity ||
+  const int64_t rows = (int64_t)need * S;
+  // (a table of 2^31 slots or more cannot be one of this pool)
+  if (g0 < 0 || need <= 0 || nb0 < 0 || rows > INT32_MAX ||
+      (int64_t)(g0 + (int64_t)need) * S > a.src_plan_capacity ||
       (int64_t)nb0 + need > a.new_bt_capacity) {
     return;
   }
-  const int U = a.row_units;
-  const int chunk = a.chunk_units;
-  const uint32_t chunk_bytes = static_cast<uint32_t>(chunk) * 16u;
-  const uint32_t magic = a.row_magic;
-  const bool unit_rows = U == 1;
-  const int tid = static_cast<int>(threadIdx.x);
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const uint8_t* pbase = a.kv + (int64_t)plane * a.plane_bytes;
+  const int32_t* plan = a.src_plan + (int64_t)g0 * S;
+  const int plane = static_cast<int>(chain / slices);
+  const int unit = (static_cast<int>(chain - (int64_t)plane * slices) << kWsh) +
+                   (lane & ((1 << kWsh) - 1));
+  const bool mine = chain < chains && unit < a.row_units;   // this lane has bytes to move
+  uint8_t* base = a.kv + (mine ? (int64_t)plane * a.plane_bytes + (int64_t)unit * 16 : 0);
 
-  // kV reads per thread of listed block lb (index within the chunk, or -1 for none): the
-  // moving rows, and for the other units the plane's first 16 bytes; returns which of the kV
-  // units move
-  auto load_block = [&](int lb, u32x4 (&regs)[kV]) -> uint32_t {
-    const int dslot0 = lb >= 0 ? dblk_s[lb] * S : 0;
-    const int pv = lb >= 0 ? plan_s[lb * S + (lane < S ? lane : S - 1)] : -1;
-    uint32_t moving = 0;
+  for (uint32_t c0 = 0; c0 < static_cast<uint32_t>(rows); c0 += kMoveRows) {
+    // the moves of rows c0 .. c0 + kMoveRows, in order: wave w holds rows
+    // w * 64 * kMoveTile + q * 64 + lane (positions clamped to the last row, all loads in
+    // flight together)
+    int src[kMoveTile], dst[kMoveTile], rank[kMoveTile];
+    const uint32_t wrow = c0 + wave * (64 * kMoveTile) + lane;
 #pragma unroll
-    for (int v = 0; v < kV; ++v) {
-      const int u = v * kCopyThreads + tid;
-      const int j = unit_rows ? u : static_cast<int>(__umulhi(static_cast<uint32_t>(u), magic));
-      const int col = u - j * U;
-      const int src = __shfl(pv, j & 63, 64);
-      const bool mv = u < chunk &&
-                      static_cast<unsigned>(src) < static_cast<unsigned>(a.num_slots) &&
-                      src != dslot0 + j;
-      const int64_t off = mv ? (int64_t)src * a.row_bytes + col * 16 : 0;
-      regs[v] = load16<true>(reinterpret_cast<const u32x4*>(pbase + off));
-      moving |= mv ? 1u << v : 0u;
+    for (int q = 0; q < kMoveTile; ++q) {
+      const int row = static_cast<int>(min(wrow + q * 64, static_cast<uint32_t>(rows) - 1));
+      const int blk = row / S;
+      src[q] = plan[row];
+      dst[q] = a.new_block_ids[nb0 + blk];
+      rank[q] = row - blk * S;
     }
-    return moving;
-  };
-  auto store_block = [&](int lb, const u32x4 (&regs)[kV], uint32_t moving) {
-    uint8_t* dptr = uniform_ptr(a.kv + (int64_t)plane * a.plane_bytes +
-                                (int64_t)dblk_s[lb] * S * a.row_bytes);
-    const __amdgpu_buffer_rsrc_t rsrc =
-        __builtin_amdgcn_make_buffer_rsrc(dptr, 0, chunk_bytes, kBufferDword3);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int v = 0; v < kV; ++v) {
-      const int u = v * kCopyThreads + tid;
-      const uint32_t off = (moving >> v) & 1u ? static_cast<uint32_t>(u) * 16u : kDropOffset;
-      __builtin_amdgcn_raw_buffer_store_b128(regs[v], rsrc, off, 0, 16);
+    for (int q = 0; q < kMoveTile; ++q) {
+      const bool ok = wrow + q * 64 < static_cast<uint32_t>(rows) &&
+                      static_cast<unsigned>(dst[q]) < static_cast<unsigned>(a.num_blocks) &&
+                      static_cast<unsigned>(src[q]) < static_cast<unsigned>(a.num_slots);
+      dst[q] = ok ? dst[q] * S + rank[q] : src[q];
     }
-  };
+    int local = 0;
+#pragma unroll
+    for (int q = 0; q < kMoveTile; ++q) {
+      const uint64_t m = __ballot(src[q] != dst[q]);
+      rank[q] = local + lanes_below(m);
+      local += __popcll(m);
+    }
+    if (lane == 0) wave_tot[wave] = local;
+    __syncthreads();   // also: every wave has walked the previous moves
+    int off = 0, total = 0;
+#pragma unroll
+    for (int i = 0; i < kWaves; ++i) {
+      const int x = wave_tot[i];
+      off += i < wave ? x : 0;
+      total += x;
+    }
+#pragma unroll
+    for (int q = 0; q < kMoveTile; ++q) {
+      if (src[q] != dst[q]) move_s[off + rank[q]] = make_int2(src[q], dst[q]);
+    }
+    // the walk reads ahead of the last move: rows of slot 0, never written
+    for (int i = total + tid; i < total + 2 * kGroup; i += kThreads) {
+      move_s[i] = make_int2(0, 0);
+    }
+    __syncthreads();
 
-  for (int c0 = 0; c0 < need; c0 += kChunkBlocks) {
-    const int nb = need - c0 < kChunkBlocks ? need - c0 : kChunkBlocks;
-    __syncthreads();  // the previous chunk is done with the LDS arrays
-    for (int i = tid; i < nb * S; i += kCopyThreads) {
-      plan_s[i] = a.src_plan[(int64_t)(g0 + c0) * S + i];
-    }
-    if (tid < nb) dblk_s[tid] = a.new_block_ids[nb0 + c0 + tid];
-    __syncthreads();
-    // which blocks move (a block with an invalid destination is left alone)
-    for (int b = wave; b < nb; b += kWaves) {
-      const int dblk = dblk_s[b];
-      const int pv = lane < S ? plan_s[b * S + lane] : -1;
-      const bool row_moves = static_cast<unsigned>(dblk) < static_cast<unsigned>(a.num_blocks) &&
-                             lane < S && static_cast<unsigned>(pv) <
-                             static_cast<unsigned>(a.num_slots) && pv != dblk * S + lane;
-      const uint64_t m = __ballot(row_moves);
-      if (lane == 0) flag_s[b] = m != 0;
-    }
-    __syncthreads();
-    if (wave == 0) {
-      const bool f = lane < nb && flag_s[lane] != 0;
-      const uint64_t m = __ballot(f);
-      if (f) list_s[lanes_below(m)] = lane;
-      if (lane == 0) nlist_s = __popcll(m);
-    }
-    __syncthreads();
-    const int nl = nlist_s;
-    if (nl == 0) continue;
-    u32x4 ra[kV], rb[kV];
-    uint32_t ma = load_block(list_s[0], ra), mb;
-    // vector-memory operations retire in order (stores included): after issuing the next
-    // block's kV reads, waiting until kV remain means this block's reads (and the previous
-    // block's stores) are done. Past the end of the list the "next" reads are of no block
-    // (-1: every unit reads the plane's first 16 bytes), so every wait count stays static.
-    for (int i = 0; i < nl; i += 2) {
-      mb = load_block(i + 1 < nl ? list_s[i + 1] : -1, rb);
-      __builtin_amdgcn_s_waitcnt(vmcnt_imm(kV));
-      __syncthreads();
-      store_block(list_s[i], ra, ma);
-      if (i + 1 < nl) {
-        ma = load_block(i + 2 < nl ? list_s[i + 2] : -1, ra);
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm(kV));
-        __syncthreads();
-        store_block(list_s[i + 1], rb, mb);
+    // a group: kV instructions of kRows rows
+    typedef u32x4 Group[kV];
+    const int2* mine_s = move_s + (lane >> kWsh);
+    auto load = [&](int i, Group& g) {
+      int from[kV];
+#pragma unroll
+      for (int v = 0; v < kV; ++v) from[v] = mine_s[i * kGroup + v * kRows].x;
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int v = 0; v < kV; ++v) {
+        g[v] = load16<true>(
+            reinterpret_cast<const u32x4*>(base + (int64_t)from[v] * a.row_bytes));
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    auto put = [&](int slot, u32x4 val) {
+      u32x4* p = reinterpret_cast<u32x4*>(base + (int64_t)slot * a.row_bytes);
+      if constexpr (kFew) {
+        *p = val;
+      } else {
+        __builtin_nontemporal_store(val, p);
+      }
+    };
+    auto store = [&](int i, const Group& g) {
+      int to[kV];
+#pragma unroll
+      for (int v = 0; v < kV; ++v) to[v] = mine_s[i * kGroup + v * kRows].y;
+#pragma unroll
+      for (int v = 0; v < kV; ++v) {
+        put(to[v], g[v]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    const int rows_left = total - (lane >> kWsh);
+    auto store_last = [&](int i, const Group& g) {   // the moves that exist
+#pragma unroll
+      for (int v = 0; v < kV; ++v) {
+        const int to = mine_s[i * kGroup + v * kRows].y;
+        if (i * kGroup + v * kRows < rows_left) put(to, g[v]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    auto wait = [](auto n) {
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm(decltype(n)::value));
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    using None = std::integral_constant<int, 0>;
+    using One = std::integral_constant<int, kV>;
+    using Two = std::integral_constant<int, 2 * kV>;
+    // Vector-memory operations retire in order, stores included: a group's reads have
+    // returned when at most the operations issued after them are left, which are the kV
+    // stores of the group before (from the second group on) and the kV reads of the next.
+    if (total > 0 && mine) {
+      const int last = (total - 1) / kGroup;
+      Group x, y;
+      load(0, x);
+      load(1, y);
+      wait(One{});
+      if (last == 0) {
+        store_last(0, x);
+      } else {
+        store(0, x);
+        int i = 1;   // y holds group i
+        for (; i + 2 <= last; i += 2) {
+          load(i + 1, x);
+          wait(Two{});
+          store(i, y);
+          load(i + 2, y);
+          wait(Two{});
+          store(i + 1, x);
+        }
+        load(i + 1, x);
+        wait(Two{});
+        store_last(i, y);
+        wait(None{});
+        store_last(i + 1, x);
       }
     }
   }
+}
+
+// Chains of the row walk: slices of 64 units (1 KiB), or the whole row where it is shorter, cut
+// down to 128-byte slices until the launch has kInplaceChains chains (bf16, 9 requests of
+// 5-23K, 32 layers x 8 x 128: 1,416 us with 4,608 chains, 1,398 with 18,432; bf16, 38 of 8K, 16
+// layers: 1,590 and 1,561). Rows that are no whole number of 128-byte lines lose more to lines
+// shared by slices: those are cut, down to 64 bytes, for kInplaceOddChains only (960-byte rows,
+// 168 pairs: 78 us in 168 chains, 46 in 672; 2 pairs: 778 us in 2, 253 in 30).
+constexpr int64_t kInplaceChains = 16384;
+constexpr int64_t kInplaceOddChains = 512;
+constexpr int64_t kInplaceFewChains = 1024;
+constexpr int64_t kMaxInplaceGrid = 1 << 22;
+
+template <bool kFew>
+auto inplace_rows_kernel(int wsh) -> void (*)(InplaceArgs, int, int64_t) {
+  switch (wsh) {
+    case 0: return repack_inplace_rows_kernel<kInplaceGroup, 0, kFew>;
+    case 1: return repack_inplace_rows_kernel<kInplaceGroup, 1, kFew>;
+    case 2: return repack_inplace_rows_kernel<kInplaceGroup, 2, kFew>;
+    case 3: return repack_inplace_rows_kernel<kInplaceGroup, 3, kFew>;
+    case 4: return repack_inplace_rows_kernel<kInplaceGroup, 4, kFew>;
+    case 5: return repack_inplace_rows_kernel<kInplaceGroup, 5, kFew>;
+    default: return repack_inplace_rows_kernel<kInplaceGroup, 6, kFew>;
+  }
+}
+
+hipError_t launch_inplace_rows(const InplaceArgs& a, hipStream_t stream) {
+  int wsh = 0;   // log2 units of a slice
+  while (wsh < 6 && (1 << wsh) < a.row_units) ++wsh;
+  const int64_t pairs = (int64_t)a.num_reqs * a.num_planes;
+  auto slices_of = [&](int sh) { return (a.row_units + (1 << sh) - 1) >> sh; };
+  const bool lines = a.row_units % 8 == 0;
+  const int64_t most = lines ? kInplaceChains : kInplaceOddChains;
+  while (wsh > (lines ? 3 : 2) && pairs * slices_of(wsh) < most) --wsh;
+  const int slices = slices_of(wsh);
+  const bool few = pairs * slices < kInplaceFewChains;
+  const int threads = few ? 64 : kCopyThreads;
+  const int waves = threads / 64;
+  const int64_t items = a.num_reqs * (((int64_t)a.num_planes * slices + waves - 1) / waves);
+  // (a launch dimension holds 2^32 threads)
+  const int64_t gx = items < kMaxInplaceGrid ? items : kMaxInplaceGrid;
+  const dim3 grid(static_cast<unsigned>(gx), static_cast<unsigned>((items + gx - 1) / gx));
+  const auto kernel = few ? inplace_rows_kernel<true>(wsh) : inplace_rows_kernel<false>(wsh);
+  hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, stream, a, slices, items);
+  return hipGetLastError();
 }
 
 template <int kV, bool kSmallS>
 hipError_t launch_inplace_v(const InplaceArgs& a, int variant, hipStream_t stream) {
   const int64_t grid = (int64_t)a.num_reqs * a.num_planes;
   const int64_t chunk_bytes = (int64_t)a.chunk_units * 16;
-  // default: pipelined registers for S <= 64, else registers (measured fastest); LDS double
-  // buffer when asked and two fit
+  // LDS double buffer when asked and two fit
   int stage = variant == 1 ? kLdsDouble : variant == 2 ? kLdsSingle : kRegisters;
   if (stage == kLdsDouble && chunk_bytes * 2 > kMaxInplaceChunkBytes) stage = kLdsSingle;
   const dim3 g(static_cast<unsigned>(grid));
   const dim3 t(kCopyThreads);
-  if constexpr (kSmallS) {
-    if (variant == 4 || variant == 0) {
-      auto kernel = repack_inplace_pipe_kernel<kV>;
-      hipLaunchKernelGGL(kernel, g, t, 0, stream, a);
-      return hipGetLastError();
-    }
-  }
   if (stage == kLdsDouble) {
     auto kernel = repack_inplace_kernel<kV, kSmallS, kLdsDouble>;
     hipLaunchKernelGGL(kernel, g, t, static_cast<size_t>(2 * chunk_bytes), stream, a);
@@ -698,6 +805,7 @@ hipError_t launch_repack_inplace(const InplaceArgs& a, int variant, hipStream_t 
   if (variant < 0 || variant > 4) return hipErrorInvalidValue;
   if ((int64_t)a.num_reqs * a.num_planes <= 0) return hipSuccess;
   if ((int64_t)a.chunk_units * 16 > kMaxInplaceChunkBytes) return hipErrorInvalidValue;
+  if (variant == 0 || variant == 4) return launch_inplace_rows(a, stream);
   return a.block_size <= 64 ? launch_inplace_s<true>(a, variant, stream)
                             : launch_inplace_s<false>(a, variant, stream);
 }

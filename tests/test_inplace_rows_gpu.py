@@ -1,0 +1,45 @@
+"""GPU parity of the in-place copy's row walk where its groups, staged move lists and column
+slices end: plan and every KV byte against the oracle, exactly."""
+import numpy as np
+import pytest
+
+from gpu_helpers import full_parity
+from paper_2608_13263_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _all_move(S, n):
+    return [0] * S + [1] * n   # a block shorter: admitted, and each of the n rows moves
+
+
+# (heads, dim, dtype, layers): 16-byte rows; 48; 80; 128; 256; 960 (no whole lines); 1 KiB; 4 KiB
+ROWS = [(1, 8, "fp16", 1), (3, 8, "fp16", 2), (5, 8, "bf16", 1), (2, 64, "fp8_e4m3", 1),
+        (1, 128, "bf16", 2), (5, 96, "bf16", 1), (4, 128, "bf16", 1), (16, 128, "fp16", 1)]
+
+
+@pytest.mark.parametrize("heads,dim,dtype,layers", ROWS)
+def test_group_and_list_edges(heads, dim, dtype, layers):
+    """Chains of k groups of moves and one more or less (groups are 8 instructions of 1 to 64
+    rows: 8 to 512), of one staged list (1,024 or 2,048 rows) and one more or less, and lists
+    without a move in the middle of a chain."""
+    S = 16
+    shape = W.KVShape(layers, heads, dim, S, dtype)
+    counts = [1, 7, 8, 9, 31, 32, 33, 63, 64, 65, 128, 129, 511, 512, 513, 1023, 1024, 1025,
+              2047, 2048, 2049]
+    masks = [_all_move(S, n) for n in counts]
+    masks.append([1] * 3000 + [0] * S + [1] * 100)                 # lists that move nothing
+    masks.append([1] * 2048 + [0] * (S + 1) + [1] * 2047)
+    masks.append([1] * 50)                                         # not admitted
+    full_parity(W.from_masks(masks, shape, free_blocks=0, seed=heads), seed=dim, inplace=True)
+
+
+@pytest.mark.parametrize("S", [8, 24, 64, 96])
+@pytest.mark.parametrize("reqs", [2, 40])
+def test_few_and_many_chains(S, reqs):
+    """Either side of the switch from one-wave to four-wave workgroups (1,024 chains: 2 requests
+    x 8 planes x 4 slices, 40 x 8 x 4), block sizes above a wave too."""
+    rng = np.random.default_rng(S * 100 + reqs)
+    shape = W.KVShape(4, 2, 128, S, "bf16")
+    masks = [list((rng.random(int(n)) < 0.5).astype(int)) for n in rng.integers(1, 900, reqs)]
+    full_parity(W.from_masks(masks, shape, free_blocks=3, seed=S), seed=reqs, inplace=True)
