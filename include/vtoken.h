@@ -234,6 +234,10 @@ vtoken_status vtoken_build_token_table_inplace(const vtoken_cache* cache,
                                                const vtoken_plan* plan, hipStream_t stream);
 vtoken_status vtoken_repack_inplace(const vtoken_cache* cache, const vtoken_batch* batch,
                                     const vtoken_plan* plan, hipStream_t stream);
+/* vtoken_repack_inplace and vtoken_free_blocks in one launch; freed as in vtoken_free_blocks. */
+vtoken_status vtoken_repack_inplace_free(const vtoken_cache* cache, const vtoken_batch* batch,
+                                         const vtoken_plan* plan, int32_t* freed,
+                                         int64_t freed_capacity, hipStream_t stream);
 
 /* Tuning entry for the copy of step 2; vtoken_repack uses the defaults (all fields 0).
  *   variant: cache policy of the copy's 16-byte loads and stores (CDNA4 cache-policy bits)

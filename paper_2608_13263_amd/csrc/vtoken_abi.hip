@@ -138,15 +138,13 @@ vtoken_status vtoken_repack_inplace(const vtoken_cache* cache, const vtoken_batc
   return vtoken_repack_inplace_ex(cache, batch, plan, nullptr, stream);
 }
 
-vtoken_status vtoken_repack_inplace_ex(const vtoken_cache* cache, const vtoken_batch* batch,
-                                       const vtoken_plan* plan,
-                                       const vtoken_repack_options* options,
-                                       hipStream_t stream) {
-  const int variant = options != nullptr ? options->variant : 0;
-  if (variant < 0 || variant > 4 || (options != nullptr && (options->grid != 0 ||
-                                                            options->order != 0))) {
-    return VTOKEN_ERR_ARGUMENT;
-  }
+}  // extern "C"
+
+namespace {
+// The in-place copy, and with with_free the freed list in the same launch.
+vtoken_status repack_in_place(const vtoken_cache* cache, const vtoken_batch* batch,
+                              const vtoken_plan* plan, int variant, bool with_free,
+                              int32_t* freed, int64_t freed_capacity, hipStream_t stream) {
   vtoken_status s = check_cache(cache);
   if (s != VTOKEN_OK) return s;
   if ((s = check_batch(batch)) != VTOKEN_OK) return s;
@@ -154,7 +152,7 @@ vtoken_status vtoken_repack_inplace_ex(const vtoken_cache* cache, const vtoken_b
   const int64_t row = (int64_t)cache->num_kv_heads * cache->head_dim * cache->elem_bytes;
   if ((int64_t)cache->block_size * row > vtoken::kMaxInplaceChunkBytes) return VTOKEN_ERR_SHAPE;
   if ((int64_t)batch->num_reqs * 2 * cache->num_layers > kInt32Limit) return VTOKEN_ERR_SHAPE;
-  vtoken::InplaceArgs a;
+  vtoken::InplaceArgs a = {};
   a.kv = static_cast<uint8_t*>(cache->kv);
   a.row_bytes = row;
   a.plane_bytes = (int64_t)cache->num_blocks * cache->block_size * row;
@@ -174,7 +172,41 @@ vtoken_status vtoken_repack_inplace_ex(const vtoken_cache* cache, const vtoken_b
   a.new_bt_indptr = plan->new_bt_indptr;
   a.admitted = plan->admitted;
   a.counters = plan->counters;
+  if (with_free) {
+    a.free_reqs = batch->num_reqs;
+    a.num_bt_entries = batch->num_bt_entries;
+    a.bt_indptr = batch->bt_indptr;
+    a.block_ids = batch->block_ids;
+    a.freed_indptr = plan->freed_indptr;
+    a.freed = freed;
+    a.freed_capacity = freed_capacity;
+  }
   return hip_status(vtoken::launch_repack_inplace(a, variant, stream));
+}
+}  // namespace
+
+extern "C" {
+
+vtoken_status vtoken_repack_inplace_ex(const vtoken_cache* cache, const vtoken_batch* batch,
+                                       const vtoken_plan* plan,
+                                       const vtoken_repack_options* options,
+                                       hipStream_t stream) {
+  const int variant = options != nullptr ? options->variant : 0;
+  if (variant < 0 || variant > 4 || (options != nullptr && (options->grid != 0 ||
+                                                            options->order != 0))) {
+    return VTOKEN_ERR_ARGUMENT;
+  }
+  return repack_in_place(cache, batch, plan, variant, false, nullptr, 0, stream);
+}
+
+vtoken_status vtoken_repack_inplace_free(const vtoken_cache* cache, const vtoken_batch* batch,
+                                         const vtoken_plan* plan, int32_t* freed,
+                                         int64_t freed_capacity, hipStream_t stream) {
+  vtoken_status s = check_batch(batch);
+  if (s != VTOKEN_OK) return s;
+  if (freed_capacity < batch->num_bt_entries) return VTOKEN_ERR_CAPACITY;
+  if (batch->num_bt_entries > 0 && freed == nullptr) return VTOKEN_ERR_NULL;
+  return repack_in_place(cache, batch, plan, 0, true, freed, freed_capacity, stream);
 }
 
 }  // extern "C"

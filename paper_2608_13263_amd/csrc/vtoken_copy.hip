@@ -550,7 +550,13 @@ void repack_inplace_rows_kernel(InplaceArgs a, int slices, int64_t items) {
   const int64_t chains = (int64_t)a.num_planes * slices;
   const int64_t per_req = (chains + kWaves - 1) / kWaves;   // workgroups of a request
   const int64_t w = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
-  if (w >= items) return;
+  if (w >= items) {   // the freed list (vtoken_repack_inplace_free)
+    if (w - items < a.free_reqs) {
+      write_freed_blocks(static_cast<int>(w - items), a.admitted, a.bt_indptr, a.freed_indptr,
+                         a.block_ids, a.num_bt_entries, a.freed, a.freed_capacity);
+    }
+    return;
+  }
   // longest chains first: workgroups k * per_req .. take the request with the k-th longest
   // chain (ties by index), so the last workgroups to start are short ones and the tail of the
   // launch is short; for R <= 256 only (every workgroup ranks the requests)
@@ -759,8 +765,9 @@ hipError_t launch_inplace_rows(const InplaceArgs& a, hipStream_t stream) {
   const int waves = threads / 64;
   const int64_t items = a.num_reqs * (((int64_t)a.num_planes * slices + waves - 1) / waves);
   // (a launch dimension holds 2^32 threads)
-  const int64_t gx = items < kMaxInplaceGrid ? items : kMaxInplaceGrid;
-  const dim3 grid(static_cast<unsigned>(gx), static_cast<unsigned>((items + gx - 1) / gx));
+  const int64_t total = items + a.free_reqs;
+  const int64_t gx = total < kMaxInplaceGrid ? total : kMaxInplaceGrid;
+  const dim3 grid(static_cast<unsigned>(gx), static_cast<unsigned>((total + gx - 1) / gx));
   const auto kernel = few ? inplace_rows_kernel<true>(wsh) : inplace_rows_kernel<false>(wsh);
   hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, stream, a, slices, items);
   return hipGetLastError();

@@ -143,6 +143,16 @@ struct InplaceArgs {
   const int32_t* new_bt_indptr;
   const int32_t* admitted;
   int32_t* counters;        // read; the status word is set if the plan's mode does not match
+  // the freed list in the same launch (vtoken_repack_inplace_free; variants 0 and 4), by the
+  // free_reqs workgroups after the copy's; 0: none. freed may be null when the batch has no
+  // table entries (nothing to write)
+  int32_t free_reqs;
+  int64_t num_bt_entries;
+  const int32_t* bt_indptr;
+  const int32_t* block_ids;
+  const int32_t* freed_indptr;
+  int32_t* freed;
+  int64_t freed_capacity;
 };
 
 // Largest chunk (S * row_bytes) the in-place copy stages through LDS.

@@ -3,7 +3,7 @@ slices end: plan and every KV byte against the oracle, exactly."""
 import numpy as np
 import pytest
 
-from gpu_helpers import full_parity
+from gpu_helpers import full_parity, gpu_pass, plan_to_host, torch
 from paper_2608_13263_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
@@ -43,3 +43,26 @@ def test_few_and_many_chains(S, reqs):
     shape = W.KVShape(4, 2, 128, S, "bf16")
     masks = [list((rng.random(int(n)) < 0.5).astype(int)) for n in rng.integers(1, 900, reqs)]
     full_parity(W.from_masks(masks, shape, free_blocks=3, seed=S), seed=reqs, inplace=True)
+
+
+@pytest.mark.parametrize("reqs", [1, 30, 600])
+def test_freed_list_in_the_copy_launch(reqs):
+    """repack_inplace_free against the copy and free_blocks in two calls: the plan, the freed list
+    and every KV byte, with a batch that releases nothing and one that admits nothing too."""
+    t = torch()
+    from paper_2608_13263_amd import binding as B
+    rng = np.random.default_rng(reqs)
+    shape = W.KVShape(2, 2, 64, 16, "bf16")
+    masks = [list((rng.random(int(n)) < 0.5).astype(int)) for n in rng.integers(1, 300, reqs)]
+    for m in (masks, [[1] * len(x) for x in masks], [[0] * len(x) for x in masks]):
+        inp = W.from_masks(m, shape, free_blocks=0, seed=reqs)
+        kv = W.kv_device(shape, inp.num_blocks, 5)
+        kv2 = kv.clone()
+        want = gpu_pass(inp, kv, inplace=True)
+        batch = B.Batch.from_inputs(inp)
+        plan = B.run_pass(B.KVCache(kv2, 2, 2, 64, 16), batch, inplace=True)
+        t.cuda.synchronize()
+        got = plan_to_host(plan, inp)
+        for k in want:
+            assert np.array_equal(got[k], want[k]), k
+        assert t.equal(kv.view(t.uint8), kv2.view(t.uint8))
