@@ -1,0 +1,125 @@
+"""GPU parity of the metadata kernels either side of their dispatch rules: slot mappings and
+appends of one launch or two, the free-list check of large batches, and the partial pass's count
+by request. Everything is exact."""
+import numpy as np
+import pytest
+
+from gpu_helpers import torch
+from paper_2608_13263_amd import workloads as W
+from test_planner_gpu import partial_parity
+
+pytestmark = pytest.mark.gpu
+
+
+def _B():
+    from paper_2608_13263_amd import binding as B
+    return B
+
+
+def _planned(masks, S=8, free=None, inplace=False):
+    B = _B()
+    shape = W.KVShape(1, 1, 8, S, "fp16")
+    inp = W.from_masks(masks, shape, free_blocks=len(masks), seed=1)
+    if free is not None:
+        inp.free_list = free(inp)
+    kv = W.kv_device(shape, inp.num_blocks, 1)
+    batch = B.Batch.from_inputs(inp)
+    plan = B.Plan.allocate(batch, S, inplace=inplace)
+    cache = B.KVCache(kv, 1, 1, 8, S)
+    (B.build_token_table_inplace if inplace else B.build_token_table)(cache, batch, plan)
+    return inp, batch, plan
+
+
+@pytest.mark.parametrize("R", [1, 63, 1024, 1025, 4096, 4097])
+@pytest.mark.parametrize("reserve", [0, 3])
+def test_slot_mapping_offsets(R, reserve):
+    """4,096 requests is the last batch whose workgroups sum the counts before theirs."""
+    t, B = torch(), _B()
+    rng = np.random.default_rng(R)
+    masks = [list((rng.random(int(n)) < 0.6).astype(int)) for n in rng.integers(1, 12, R)]
+    masks[R // 2] = list((rng.random(9000) < 0.5).astype(int))
+    inp, batch, plan = _planned(masks)
+    if reserve:
+        start, count, slots = B.build_slot_table(batch, plan, reserve)
+    else:
+        start, slots = B.build_slot_mapping(batch, plan)
+    t.cuda.synchronize()
+    ts, live = plan.token_slot.cpu().numpy(), plan.live_count.cpu().numpy()[:R]
+    want = np.concatenate([[0], np.cumsum(live + reserve)])
+    assert np.array_equal(start.cpu().numpy(), want)
+    got = slots.cpu().numpy()
+    if reserve:
+        assert np.array_equal(count.cpu().numpy()[:R], live)
+    for r in range(R):
+        s = ts[inp.tok_indptr[r]:inp.tok_indptr[r + 1]]
+        assert np.array_equal(got[want[r]:want[r] + live[r]], s[s >= 0]), r
+
+
+@pytest.mark.parametrize("R", [1, 64, 65, 128, 129])
+@pytest.mark.parametrize("full", [False, True])
+def test_append_one_launch(R, full):
+    """128 requests is the last batch of one launch; 0 to 40 new slots each, and one request
+    whose region is too small (left alone, the status says so)."""
+    t, B = torch(), _B()
+    rng = np.random.default_rng(R)
+    new = rng.integers(0, 41, R)
+    room = new + rng.integers(0, 3, R)
+    count = rng.integers(0, 20, R)
+    if full:
+        new[R // 2], room[R // 2] = 7, 6
+    start = np.concatenate([[0], np.cumsum(count + room)])
+    indptr = np.concatenate([[0], np.cumsum(new)])
+    add = rng.integers(0, 1 << 30, max(int(indptr[-1]), 1))
+    slots = np.arange(int(start[-1]) + 1)
+
+    def dev(x):
+        return t.from_numpy(np.asarray(x, dtype=np.int32)).cuda()
+    d_count, d_slots = dev(count), dev(slots)
+    status = B.append_slots(dev(start), d_count, d_slots, dev(indptr), dev(add),
+                            status=dev([77]))
+    t.cuda.synchronize()
+    for r in range(R):
+        if new[r] <= room[r]:
+            at = start[r] + count[r]
+            slots[at:at + new[r]] = add[indptr[r]:indptr[r + 1]]
+            count[r] += new[r]
+    assert int(status) == (B.STATUS_CODE["VTOKEN_ERR_CAPACITY"] if full else 0)
+    assert np.array_equal(d_count.cpu().numpy(), count)
+    assert np.array_equal(d_slots.cpu().numpy(), slots)
+
+
+@pytest.mark.parametrize("R", [256, 257, 600])
+@pytest.mark.parametrize("bad", [-1, 0, 1])
+def test_free_list_entry_outside_the_pool(R, bad):
+    """A bad entry before, at and after the last consumed one; batches whose admission is a
+    launch of its own (more than 256 short requests) look the list over beforehand."""
+    t, B = torch(), _B()
+    masks = [[1, 0] * 12] * R                       # 24 tokens, 3 blocks, 12 live: 2 blocks
+    used = 2 * R
+
+    def free(inp):
+        f = np.arange(used + 5, dtype=np.int32) % inp.num_blocks
+        f[used - 1 + bad] = inp.num_blocks if R % 2 else -1
+        return f
+    _, _, plan = _planned(masks, free=free)
+    t.cuda.synchronize()
+    c = plan.counters.cpu().tolist()
+    if bad <= 0:
+        assert c[3] == B.STATUS_CODE["VTOKEN_ERR_BLOCK_RANGE"] and c[0] == 0
+    else:
+        assert c[3] == 0 and c[0] == used
+
+
+@pytest.mark.parametrize("S,reqs,lens,shared", [
+    (16, 100, (5200, 5400), 4),       # two tiles a request, shared blocks
+    (48, 520, (1000, 1100), 0),       # one workgroup a request, S no power of two
+    (64, 20, (26500, 27500), 2),      # slots past 32 in a block, several workgroups a request
+    (4, 16, (32500, 33500), 2),       # tables of more entries than the bitmap holds
+])
+def test_partial_count_by_request(S, reqs, lens, shared):
+    """At least 2^19 tokens in long requests: counted by request."""
+    inp = W.token_table_inputs(631 + S, W.KVShape(1, 1, 8, S, "fp16"), num_reqs=reqs,
+                               len_range=lens, shared_groups=shared, group_size=3,
+                               prefix_tokens=256 if shared else 0)
+    assert inp.num_tokens >= 1 << 19
+    partial_parity(inp, label=f"count by request S={S}")
