@@ -41,12 +41,31 @@ static_assert(kPlanThreadsSplit % 64 == 0 && kPlanThreadsSplit <= kPlanThreads,
 // (Sec. 3.2: the token table's liveness bits). A request with an error stores the (negative)
 // error code as its live count, which the plan kernel picks up.
 // ------------------------------------------------------------------------------------------
-template <int kThreads>
+//
+// kCheckFree (admit_kernel follows): workgroup r also looks over the r-th share of the free list
+// and leaves the first entry outside the pool in admitted[r] (INT_MAX: none), which the admission
+// reads before it writes its flags. The one workgroup of the admission spent 13 of its 18.7 us on
+// the 170K consumed entries of a batch of 1,024 requests and 5.2M tokens; shared out they cost
+// the count launch 1 us (plan and mapping of that batch 50 -> 37 us).
+template <int kThreads, bool kCheckFree>
 __global__ __launch_bounds__(kThreads) void count_kernel(MetaArgs a) {
   __shared__ int wave_sum[kThreads / 64];
+  __shared__ int first_bad;
   const int r = blockIdx.x;
   const int tid = threadIdx.x;
   const int S = a.block_size;
+  if constexpr (kCheckFree) {
+    if (tid == 0) first_bad = INT_MAX;
+    __syncthreads();
+    const int64_t share = ((int64_t)a.free_len + a.num_reqs - 1) / a.num_reqs;
+    const int64_t j1 = min((r + 1) * share, (int64_t)a.free_len);
+    for (int64_t j = r * share + tid; j < j1; j += kThreads) {
+      const int blk = a.free_list[j];
+      if (blk < 0 || blk >= a.num_blocks) atomicMin(&first_bad, static_cast<int>(j));
+    }
+    __syncthreads();
+    if (tid == 0) a.admitted[r] = first_bad;
+  }
   const int n = a.seq_lens[r];
   const int t0 = a.tok_indptr[r], t1 = a.tok_indptr[r + 1];
   const int b0 = a.bt_indptr[r], b1 = a.bt_indptr[r + 1];
@@ -188,11 +207,13 @@ __device__ __forceinline__ Admission admit_requests(const MetaArgs& a, Count cou
 // The pass's status after the admission: the first rejected request's code, else a capacity
 // shortfall, else (checked by the workgroup that reports) a consumed free-list entry outside
 // the pool; head[0 .. head_len) is a copy of the free list's first entries in LDS, checked
-// there. The reporting workgroup writes the offsets' ends and the counters.
+// there. first_bad: the list's first entry outside the pool, where it is known. The reporting
+// workgroup writes the offsets' ends and the counters.
 __device__ __forceinline__ int admission_status(const MetaArgs& a, const Admission& adm,
                                                 int request_error, bool report,
                                                 const int32_t* head = nullptr,
-                                                int head_len = 0) {
+                                                int head_len = 0,
+                                                const int* first_bad = nullptr) {
   const int tid = threadIdx.x;
   const int S = a.block_size;
   int status = request_error;
@@ -202,7 +223,9 @@ __device__ __forceinline__ int admission_status(const MetaArgs& a, const Admissi
     status = VTOKEN_ERR_CAPACITY;
   }
   if (!report) return status;
-  if (status == 0 && !a.inplace) {
+  if (first_bad != nullptr) {
+    if (status == 0 && !a.inplace && *first_bad < adm.used) status = VTOKEN_ERR_BLOCK_RANGE;
+  } else if (status == 0 && !a.inplace) {
     // every consumed free-list entry must be a block of the pool (eight loads in flight per
     // thread)
     int bad = 0;
@@ -250,9 +273,15 @@ __global__ __launch_bounds__(kPlanThreads) void admit_kernel(MetaArgs a) {
   __shared__ int first_error_req;
   __shared__ int count_s[kAdmitStage];
   __shared__ int blocks_s[kAdmitStage];
+  __shared__ int first_bad;
   const int tid = threadIdx.x;
   const int R = a.num_reqs;
   const int staged = min(R, kAdmitStage);
+  int bad = INT_MAX;   // what count_kernel found in the free list (a thread's own requests)
+  if (!a.inplace) {
+    for (int i = tid; i < R; i += kPlanThreads) bad = min(bad, a.admitted[i]);
+  }
+  if (tid == 0) first_bad = INT_MAX;
   int c[kAdmitStage / kPlanThreads], m[kAdmitStage / kPlanThreads];
 #pragma unroll
   for (int q = 0; q < kAdmitStage / kPlanThreads; ++q) {
@@ -268,6 +297,8 @@ __global__ __launch_bounds__(kPlanThreads) void admit_kernel(MetaArgs a) {
       blocks_s[i] = m[q];
     }
   }
+  __syncthreads();   // first_bad cleared
+  if (bad != INT_MAX) atomicMin(&first_bad, bad);
   // (the admission's first barrier orders these LDS writes before every read)
   const Admission adm = admit_requests(
       a, [&](int i) { return i < kAdmitStage ? count_s[i] : a.live_count[i]; },
@@ -281,7 +312,8 @@ __global__ __launch_bounds__(kPlanThreads) void admit_kernel(MetaArgs a) {
         a.freed_indptr[i] = fr;
       },
       lds, &first_error_req);
-  admission_status(a, adm, adm.first_error == INT_MAX ? 0 : a.live_count[adm.first_error], true);
+  admission_status(a, adm, adm.first_error == INT_MAX ? 0 : a.live_count[adm.first_error], true,
+                   nullptr, 0, &first_bad);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -773,16 +805,18 @@ hipError_t launch_build(const MetaArgs& a, hipStream_t stream) {
   // requests averaging fewer than kLongRequestTokens tokens need one 16-byte load per thread
   // even at kCountThreadsShort threads, and smaller workgroups are resident more at a time
   const bool long_reqs = a.num_reqs > 0 && a.num_tokens / a.num_reqs >= kLongRequestTokens;
+  const bool admit =
+      a.num_reqs > kFusedAdmitReqs || (a.num_reqs > kFusedAdmitShortReqs && !long_reqs);
   if (a.num_reqs > 0) {
-    if (long_reqs) {
-      hipLaunchKernelGGL(count_kernel<kCountThreads>, dim3(a.num_reqs), dim3(kCountThreads), 0,
-                         stream, a);
-    } else {
-      hipLaunchKernelGGL(count_kernel<kCountThreadsShort>, dim3(a.num_reqs),
-                         dim3(kCountThreadsShort), 0, stream, a);
-    }
+    const bool check = admit && !a.inplace;
+    const auto count = long_reqs ? (check ? count_kernel<kCountThreads, true>
+                                          : count_kernel<kCountThreads, false>)
+                                 : (check ? count_kernel<kCountThreadsShort, true>
+                                          : count_kernel<kCountThreadsShort, false>);
+    hipLaunchKernelGGL(count, dim3(a.num_reqs),
+                       dim3(long_reqs ? kCountThreads : kCountThreadsShort), 0, stream, a);
   }
-  if (a.num_reqs > kFusedAdmitReqs || (a.num_reqs > kFusedAdmitShortReqs && !long_reqs)) {
+  if (admit) {
     hipLaunchKernelGGL(admit_kernel, dim3(1), dim3(kPlanThreads), 0, stream, a);
     const auto plan = pow2 ? plan_kernel<true, true, kPlanThreadsSplit>
                            : plan_kernel<false, true, kPlanThreadsSplit>;
