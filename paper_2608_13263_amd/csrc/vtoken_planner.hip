@@ -6,7 +6,8 @@
 //   pl_clear_kernel    zero the per-block live bitmaps and reference counts, the statistics
 //                      and the counters
 //   pl_count_kernel    references of every block over all tables; one bit per live slot
-//                      (a slot held live by several requests of a shared prefix counts once)
+//                      (a slot held live by several requests of a shared prefix counts once);
+//                      pl_count_request_kernel for requests of many tokens
 //   pl_blocks_request_kernel  two kinds of workgroups in one launch: up to 128 compute
 //                      n_b = live bits of each allocated block (Sec. 2.3.1, Sec. 3.3.1) and
 //                      the totals behind the waste ratio F; one per request finds its live
@@ -23,7 +24,7 @@
 //                      plan (Sec. 3.3.3, Sec. 3.2 apply_moves); tokens in tiles of 8192 with
 //                      every load of a tile in flight before its ballots
 //
-// Every kernel after pl_count_kernel does nothing once plan->counters[3] holds an error;
+// Every kernel after the count does nothing once plan->counters[3] holds an error;
 // every dereference of caller data is bounds-checked.
 #include "vtoken_internal.h"
 
@@ -108,14 +109,10 @@ __device__ __forceinline__ uint32_t wave_or(uint32_t x) {
   return r32[0] | r32[1];
 }
 
-// References of every table entry's block; one bit per live slot. Tokens go 64 to a wave:
-// the bits of the wave's tokens that fall in one block are ORed across the wave and set with
-// one atomic (up to 8 blocks per wave; a wave's remaining tokens set their bits one by one).
-template <bool kPow2>
-__global__ __launch_bounds__(256) void pl_count_kernel(PlannerArgs a) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.num_bt_entries;
-       i += stride) {
+// References of every table entry's block, by all threads of the launch.
+__device__ __forceinline__ void pl_count_refs(const PlannerArgs& a, int64_t thread,
+                                              int64_t threads) {
+  for (int64_t i = thread; i < a.num_bt_entries; i += threads) {
     const int b = a.block_ids[i];
     if (b < 0 || b >= a.num_blocks) {
       pl_error(a.counters, VTOKEN_ERR_BLOCK_RANGE);
@@ -123,13 +120,19 @@ __global__ __launch_bounds__(256) void pl_count_kernel(PlannerArgs a) {
       atomicAdd(&a.refs[b], 1);
     }
   }
+}
+
+// One bit per live slot of tokens [from, to), by waves `wave` of `waves`. Tokens go 64 to a
+// wave: the bits of the wave's tokens that fall in one block are ORed across the wave and set
+// with one atomic (up to 8 blocks per wave; a wave's remaining tokens set their bits one by one).
+template <bool kPow2>
+__device__ __forceinline__ void pl_count_waves(const PlannerArgs& a, int64_t from, int64_t to,
+                                               int64_t wave, int64_t waves) {
   const BlockDiv<kPow2> bd(a.block_size);
   const int lane = threadIdx.x & 63;
-  const int64_t waves = stride / 64;
-  for (int64_t w0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / 64 * 64;
-       w0 < a.num_tokens; w0 += waves * 64) {
+  for (int64_t w0 = from + wave * 64; w0 < to; w0 += waves * 64) {
     const int64_t t = w0 + lane;
-    const bool lv = t < a.num_tokens && a.live[t] != 0;
+    const bool lv = t < to && a.live[t] != 0;
     const int s = lv ? a.slot_in[t] : -1;
     const bool bad = lv && (s < 0 || s >= a.num_slots);
     if (bad) pl_error(a.counters, VTOKEN_ERR_SLOT);
@@ -151,6 +154,108 @@ __global__ __launch_bounds__(256) void pl_count_kernel(PlannerArgs a) {
     }
     if ((pending >> lane) & 1) {
       atomicOr(reinterpret_cast<unsigned long long*>(&a.live_bits[blk]), 1ull << off);
+    }
+  }
+}
+
+template <bool kPow2>
+__global__ __launch_bounds__(256) void pl_count_kernel(PlannerArgs a) {
+  const int64_t thread = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t threads = (int64_t)gridDim.x * blockDim.x;
+  pl_count_refs(a, thread, threads);
+  pl_count_waves<kPow2>(a, 0, a.num_tokens, thread / 64, threads / 64);
+}
+
+// The same for requests of many tokens: workgroup (r, y) takes every gridDim.y-th tile of
+// request r's tokens and collects their bits in LDS, one bitmap per entry of the request's table,
+// then sets each block's bits with one atomic. Earlier passes leave a request's tokens spread
+// over its blocks, so that nearly every token of a wave lies in another block, and one atomic
+// per token was the time of the launch: half of 256 requests of 2-8K tokens in permuted order,
+// S = 16, 34.5 us, 13.7 so. n_b[b], which the next launch fills, holds the block's entry
+// meanwhile; what is read there may be another request's (a shared block) or anything (a block of
+// no table), so an entry counts only if the request's table has the block there, and the token's
+// bit is set by itself otherwise. Tables of more than kPlCountBlocks entries take the way of the
+// launch above.
+constexpr int kPlCountThreads = 512;
+constexpr int kPlCountBlocks = 2048;
+constexpr int kPlCountTokens = 8;                                  // per thread and tile
+constexpr int kPlCountTile = kPlCountThreads * kPlCountTokens;     // 4096
+constexpr int kPlCountGrid = 512;   // workgroups wanted
+constexpr int kPlCountMinTokens = 1 << 19;
+
+template <bool kPow2>
+__global__ __launch_bounds__(kPlCountThreads) void pl_count_request_kernel(PlannerArgs a) {
+  __shared__ int ids_s[kPlCountBlocks];
+  __shared__ uint32_t bits_s[kPlCountBlocks][2];
+  constexpr int kWaves = kPlCountThreads / 64;
+  const BlockDiv<kPow2> bd(a.block_size);
+  const int tid = threadIdx.x;
+  const int r = blockIdx.x;
+  const int wg = blockIdx.y * gridDim.x + blockIdx.x;
+  pl_count_refs(a, (int64_t)wg * kPlCountThreads + tid,
+                (int64_t)gridDim.x * gridDim.y * kPlCountThreads);
+  const int t0 = a.tok_indptr[r], t1 = a.tok_indptr[r + 1];
+  const int b0 = a.bt_indptr[r], b1 = a.bt_indptr[r + 1];
+  if (blockIdx.y == 0) {   // tokens of no request (the flat count takes them too)
+    if (r == 0) {
+      pl_count_waves<kPow2>(a, 0, min(t0, a.num_tokens), tid / 64, kWaves);
+    }
+    if (r == a.num_reqs - 1) {
+      pl_count_waves<kPow2>(a, max(t1, 0), a.num_tokens, tid / 64, kWaves);
+    }
+  }
+  // (a malformed range is reported by the next launch)
+  if (t0 < 0 || t1 < t0 || t1 > a.num_tokens) return;
+  const int n = t1 - t0;
+  const int m = b1 - b0;
+  if (b0 < 0 || m < 0 || b1 > a.num_bt_entries || m > kPlCountBlocks) {
+    pl_count_waves<kPow2>(a, t0, t1, blockIdx.y * kWaves + tid / 64, (int64_t)gridDim.y * kWaves);
+    return;
+  }
+  for (int j = tid; j < m; j += kPlCountThreads) {
+    const int b = a.block_ids[b0 + j];
+    const bool in = b >= 0 && b < a.num_blocks;
+    ids_s[j] = in ? b : -1;
+    bits_s[j][0] = 0;
+    bits_s[j][1] = 0;
+    if (in) a.n_b[b] = j;
+  }
+  __syncthreads();
+  for (int base = blockIdx.y * kPlCountTile; base < n; base += gridDim.y * kPlCountTile) {
+    uint8_t lv[kPlCountTokens];
+    int sl[kPlCountTokens], at[kPlCountTokens];
+#pragma unroll
+    for (int q = 0; q < kPlCountTokens; ++q) {
+      const int p = min(base + q * kPlCountThreads + tid, n - 1);
+      lv[q] = a.live[t0 + p];
+      sl[q] = a.slot_in[t0 + p];
+    }
+#pragma unroll
+    for (int q = 0; q < kPlCountTokens; ++q) {
+      const bool valid = sl[q] >= 0 && sl[q] < a.num_slots;
+      at[q] = a.n_b[valid ? bd.div(sl[q]) : 0];
+    }
+#pragma unroll
+    for (int q = 0; q < kPlCountTokens; ++q) {
+      if (base + q * kPlCountThreads + tid >= n || lv[q] == 0) continue;
+      if (sl[q] < 0 || sl[q] >= a.num_slots) {
+        pl_error(a.counters, VTOKEN_ERR_SLOT);
+        continue;
+      }
+      const int blk = bd.div(sl[q]), off = bd.mod(sl[q]);
+      if (static_cast<unsigned>(at[q]) < static_cast<unsigned>(m) && ids_s[at[q]] == blk) {
+        atomicOr(&bits_s[at[q]][off >> 5], 1u << (off & 31));
+      } else {
+        atomicOr(reinterpret_cast<unsigned long long*>(&a.live_bits[blk]), 1ull << off);
+      }
+    }
+  }
+  __syncthreads();
+  for (int j = tid; j < m; j += kPlCountThreads) {
+    const unsigned long long bits =
+        (static_cast<unsigned long long>(bits_s[j][1]) << 32) | bits_s[j][0];
+    if (bits != 0) {   // (ids_s[j] is a block of the pool)
+      atomicOr(reinterpret_cast<unsigned long long*>(&a.live_bits[ids_s[j]]), bits);
     }
   }
 }
@@ -416,6 +521,33 @@ __global__ __launch_bounds__(kPlTableThreads) void pl_table_kernel(PlannerArgs a
     for (int i = tid; i < need; i += kPlTableThreads) dest_s[i] = a.free_list[d0 + i];
   }
 
+  if (!adm) {
+    // nothing moves: the old table, every live token where it is; no ranks and no barriers
+    // (256 requests of 2-8K tokens, none admitted: 13.9 us with them, 6.7 without)
+    for (int j = tid; j < m; j += kPlTableThreads) {
+      const int b = a.block_ids[b0 + j];
+      if (b >= 0 && b < a.num_blocks) a.selected[b] = 0;
+      if (nb0 + j < a.new_bt_capacity) a.new_block_ids[nb0 + j] = b;
+    }
+    for (int base = 0; base < n; base += kPlTile) {
+      uint8_t lv[kPlBallots];
+      int sl[kPlBallots];
+#pragma unroll
+      for (int q = 0; q < kPlBallots; ++q) {
+        const int pc = min(base + q * kPlTableThreads + tid, n - 1);
+        lv[q] = a.live[t0 + pc];
+        sl[q] = a.slot_in[t0 + pc];
+      }
+#pragma unroll
+      for (int q = 0; q < kPlBallots; ++q) {
+        const int p = base + q * kPlTableThreads + tid;
+        const bool valid = sl[q] >= 0 && sl[q] < a.num_slots;
+        if (p < n) a.token_slot[t0 + p] = lv[q] != 0 && valid ? sl[q] : -1;
+      }
+    }
+    return;
+  }
+
   // sources: the first k candidates in table order; kept blocks and released sources
   int cand_carry = 0, keep_carry = 0, sel_carry = 0;
   for (int base = 0; base < m; base += kPlTableThreads) {
@@ -525,9 +657,22 @@ hipError_t launch_planner(const PlannerArgs& a, hipStream_t stream) {
   };
   hipLaunchKernelGGL(pl_clear_kernel, dim3(grid_for(a.num_blocks)), dim3(256), 0, stream, a);
   const bool pow2 = (a.block_size & (a.block_size - 1)) == 0;
-  hipLaunchKernelGGL(pow2 ? pl_count_kernel<true> : pl_count_kernel<false>,
-                     dim3(grid_for((int64_t)a.num_bt_entries + a.num_tokens)), dim3(256), 0,
-                     stream, a);
+  // by request for batches of many tokens in long requests: its three dependent reads make it
+  // 2 us slower at 25K to 220K tokens (3, 10 and 32 requests), the wave-by-wave count takes the
+  // longer the more tokens there are (5.9 us at 164K, 34.5 at 1.3M)
+  const int64_t mean = a.num_reqs > 0 ? a.num_tokens / a.num_reqs : 0;
+  if (a.num_tokens >= kPlCountMinTokens && mean >= kLongRequestTokens) {
+    int64_t split = (kPlCountGrid + a.num_reqs - 1) / a.num_reqs;
+    const int64_t tiles = (mean + kPlCountTile - 1) / kPlCountTile;
+    split = split < tiles ? split : tiles;
+    hipLaunchKernelGGL(pow2 ? pl_count_request_kernel<true> : pl_count_request_kernel<false>,
+                       dim3(a.num_reqs, static_cast<unsigned>(split)), dim3(kPlCountThreads), 0,
+                       stream, a);
+  } else {
+    hipLaunchKernelGGL(pow2 ? pl_count_kernel<true> : pl_count_kernel<false>,
+                       dim3(grid_for((int64_t)a.num_bt_entries + a.num_tokens)), dim3(256), 0,
+                       stream, a);
+  }
   // at most 128 workgroups: each adds its totals with two atomics on the same two words
   const unsigned blocks_grid = grid_for(a.num_blocks) < 128u ? grid_for(a.num_blocks) : 128u;
   hipLaunchKernelGGL(pl_blocks_request_kernel,
