@@ -1170,8 +1170,8 @@ def run_inplace(args, inp, kv, cache, batch, plan, stream):
     R = inp.num_reqs
     repacked = int((plan.live_count[:R].long() * plan.admitted[:R].long()).sum())
     bytes_alg = 2 * moved * sh.token_bytes
-    pipelined = sh.block_size <= 64 and args.variant in (0, 4)
-    inplace_kernel = "repack_inplace_pipe_kernel" if pipelined else "repack_inplace_kernel"
+    inplace_kernel = "repack_inplace_rows_kernel" if args.variant in (0, 4) else \
+        "repack_inplace_kernel"
     out = {
         "metric": "repacked KV GB/s (read+write) as % of HBM peak; live tokens repacked/ms",
         "mode": "inplace", "value": round(bytes_alg / (step_ms / 1e3) / 1e9, 2), "unit": "GB/s",

@@ -122,7 +122,7 @@ __device__ inline void write_freed_blocks(int r, const int32_t* admitted,
   }
 }
 
-// Arguments of the in-place copy: one workgroup per (request, plane) chain.
+// Arguments of the in-place copy.
 struct InplaceArgs {
   uint8_t* kv;
   int64_t plane_bytes;
@@ -327,7 +327,7 @@ __host__ __device__ constexpr int decode_grid_splits(int splits) {
 __host__ __device__ constexpr int64_t decode_grid_groups(int64_t n) { return (n + 7) / 8 * 8; }
 
 hipError_t launch_build(const MetaArgs& a, hipStream_t stream);
-// variant: 0 default, 1 LDS double buffer, 2 LDS single buffer, 3 registers
+// variant: 0 default (4), 1 LDS double buffer, 2 LDS single buffer, 3 registers, 4 row walk
 hipError_t launch_repack_inplace(const InplaceArgs& a, int variant, hipStream_t stream);
 hipError_t launch_free(const MetaArgs& a, int32_t* freed, int64_t freed_capacity,
                        hipStream_t stream);
