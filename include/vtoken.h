@@ -363,7 +363,11 @@ vtoken_status vtoken_build_slot_mapping(const vtoken_batch* batch, const vtoken_
  * append_slots[append_indptr[r] .. append_indptr[r+1]) (device, int32) to request r's region
  * and adds their number to slot_count[r]; a request whose region would overflow is left
  * unchanged and *status (device int32, written by the call) becomes VTOKEN_ERR_CAPACITY (a
- * rebuild is due), else 0. Decode reads a slot table with vtoken_decode.slot_count set. */
+ * rebuild is due), else 0. Decode reads a slot table with vtoken_decode.slot_count set.
+ * vtoken_append_slots_n is the same call with the number of new slots, append_indptr[num_reqs]
+ * (or a larger number, such as the length of append_slots; negative: unknown, as
+ * vtoken_append_slots has it). It changes no result: few new slots for few requests are then
+ * appended in one launch instead of two. */
 vtoken_status vtoken_build_slot_table(const vtoken_batch* batch, const vtoken_plan* plan,
                                       int32_t reserve, int32_t* slot_start, int32_t* slot_count,
                                       int32_t* slots, int64_t slots_capacity,
@@ -372,6 +376,10 @@ vtoken_status vtoken_append_slots(int32_t num_reqs, const int32_t* append_indptr
                                   const int32_t* append_slots, const int32_t* slot_start,
                                   int32_t* slot_count, int32_t* slots, int32_t* status,
                                   hipStream_t stream);
+vtoken_status vtoken_append_slots_n(int32_t num_reqs, int64_t num_new,
+                                    const int32_t* append_indptr, const int32_t* append_slots,
+                                    const int32_t* slot_start, int32_t* slot_count,
+                                    int32_t* slots, int32_t* status, hipStream_t stream);
 
 /* Decode attention of one layer over the paged cache through a slot mapping: for request r
  * and query head qh (GQA: KV head qh / (num_q_heads / num_kv_heads)),

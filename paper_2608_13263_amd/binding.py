@@ -135,6 +135,10 @@ _SIGNATURES = {
     "vtoken_append_slots": (ctypes.c_int32, [ctypes.c_int32, ctypes.c_void_p, ctypes.c_void_p,
                                              ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p,
                                              ctypes.c_void_p, ctypes.c_void_p]),
+    "vtoken_append_slots_n": (ctypes.c_int32, [ctypes.c_int32, ctypes.c_int64, ctypes.c_void_p,
+                                               ctypes.c_void_p, ctypes.c_void_p,
+                                               ctypes.c_void_p, ctypes.c_void_p,
+                                               ctypes.c_void_p, ctypes.c_void_p]),
     "vtoken_decode_workspace_bytes": (ctypes.c_int64, [ctypes.c_int32, ctypes.c_int32,
                                                        ctypes.c_int32, ctypes.c_int32]),
     "vtoken_paged_decode": (ctypes.c_int32, [ctypes.POINTER(CCache), ctypes.POINTER(CDecode),
@@ -464,9 +468,10 @@ def append_slots(slot_start, slot_count, slots, append_indptr, append_slots, sta
     if status is None:
         status = torch.empty(1, dtype=torch.int32, device=slots.device)
     R = int(append_indptr.numel()) - 1
-    _check(lib.vtoken_append_slots(R, _ptr(append_indptr), _ptr(append_slots),
-                                   _ptr(slot_start), _ptr(slot_count), _ptr(slots),
-                                   _ptr(status), _stream(stream)), "vtoken_append_slots")
+    most = 0 if append_slots is None else int(append_slots.numel())
+    _check(lib.vtoken_append_slots_n(R, most, _ptr(append_indptr), _ptr(append_slots),
+                                     _ptr(slot_start), _ptr(slot_count), _ptr(slots),
+                                     _ptr(status), _stream(stream)), "vtoken_append_slots")
     return status
 
 

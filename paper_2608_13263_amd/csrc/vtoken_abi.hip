@@ -374,6 +374,14 @@ vtoken_status vtoken_append_slots(int32_t num_reqs, const int32_t* append_indptr
                                   const int32_t* append_slots, const int32_t* slot_start,
                                   int32_t* slot_count, int32_t* slots, int32_t* status,
                                   hipStream_t stream) {
+  return vtoken_append_slots_n(num_reqs, -1, append_indptr, append_slots, slot_start, slot_count,
+                               slots, status, stream);
+}
+
+vtoken_status vtoken_append_slots_n(int32_t num_reqs, int64_t num_new,
+                                    const int32_t* append_indptr, const int32_t* append_slots,
+                                    const int32_t* slot_start, int32_t* slot_count,
+                                    int32_t* slots, int32_t* status, hipStream_t stream) {
   if (num_reqs < 0) return VTOKEN_ERR_SHAPE;
   if (status == nullptr || append_indptr == nullptr) return VTOKEN_ERR_NULL;
   if (num_reqs > 0 && (append_slots == nullptr || slot_start == nullptr ||
@@ -388,7 +396,7 @@ vtoken_status vtoken_append_slots(int32_t num_reqs, const int32_t* append_indptr
   a.slot_count = slot_count;
   a.slots = slots;
   a.status = status;
-  return hip_status(vtoken::launch_append_slots(a, stream));
+  return hip_status(vtoken::launch_append_slots(a, num_new, stream));
 }
 
 int64_t vtoken_decode_workspace_bytes(int32_t num_reqs, int32_t num_q_heads, int32_t head_dim,

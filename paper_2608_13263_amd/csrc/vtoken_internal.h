@@ -253,7 +253,8 @@ struct PlannerArgs {
 hipError_t launch_planner(const PlannerArgs& a, hipStream_t stream);
 
 hipError_t launch_slot_mapping(const SlotMapArgs& a, hipStream_t stream);
-hipError_t launch_append_slots(const AppendArgs& a, hipStream_t stream);
+// num_new: at least the slots the call appends, negative if unknown; it only picks the launch
+hipError_t launch_append_slots(const AppendArgs& a, int64_t num_new, hipStream_t stream);
 hipError_t launch_paged_decode(const AttnArgs& a, hipStream_t stream);
 // The library-held decode workspace (vtoken_paged_decode_noalloc): its size, and its address
 // on the device of `stream` (looked up on the first call per device; allocates nothing).

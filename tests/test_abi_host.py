@@ -306,6 +306,13 @@ def test_slot_table_and_append_reject_bad_arguments():
         B.STATUS_CODE["VTOKEN_ERR_NULL"]
     assert lib.vtoken_append_slots(2, p, None, p, p, p, p, None) == \
         B.STATUS_CODE["VTOKEN_ERR_NULL"]
+    for new in (-1, 2, 1 << 40):   # the count of new slots changes no check
+        assert lib.vtoken_append_slots_n(-1, new, p, p, p, p, p, p, None) == \
+            B.STATUS_CODE["VTOKEN_ERR_SHAPE"]
+        assert lib.vtoken_append_slots_n(2, new, p, p, p, p, p, None, None) == \
+            B.STATUS_CODE["VTOKEN_ERR_NULL"]
+        assert lib.vtoken_append_slots_n(2, new, p, None, p, p, p, p, None) == \
+            B.STATUS_CODE["VTOKEN_ERR_NULL"]
 
 
 def test_binding_fails_loudly_without_library(tmp_path):

@@ -58,8 +58,8 @@ def test_slot_mapping_offsets(R, reserve):
 @pytest.mark.parametrize("R", [1, 64, 65, 128, 129])
 @pytest.mark.parametrize("full", [False, True])
 def test_append_one_launch(R, full):
-    """128 requests is the last batch of one launch; 0 to 40 new slots each, and one request
-    whose region is too small (left alone, the status says so)."""
+    """0 to 40 new slots each, in one launch or two, and one request whose region is too small
+    (left alone, the status says so)."""
     t, B = torch(), _B()
     rng = np.random.default_rng(R)
     new = rng.integers(0, 41, R)
@@ -86,6 +86,62 @@ def test_append_one_launch(R, full):
     assert int(status) == (B.STATUS_CODE["VTOKEN_ERR_CAPACITY"] if full else 0)
     assert np.array_equal(d_count.cpu().numpy(), count)
     assert np.array_equal(d_slots.cpu().numpy(), slots)
+
+
+@pytest.mark.parametrize("spread", ["even", "one", "spare", "unordered"])
+@pytest.mark.parametrize("total", [1, 128, 129, 256, 257, 2048, 2049, 16384, 16385])
+@pytest.mark.parametrize("R", [1, 2, 3, 8, 64, 65, 128, 129])
+def test_append_by_number_of_new_slots(R, total, spread):
+    """One launch takes up to 16,384 new slots of one request, 2,048 of 8, 256 of 64 and 128 of
+    128 (16 for each of a request's 8 to 1,024 threads): spread evenly, nearly all in one
+    request, in a buffer with spare entries at its end, and ranges that are not one after another
+    (a negative count, then the same slots once more). The entry without the number gives the
+    same."""
+    t, B = torch(), _B()
+    rng = np.random.default_rng(10 * R + total)
+    most = total // 2 if spread in ("spare", "unordered") else total
+    new = np.full(R, most // R)
+    new[:most % R] += 1
+    if spread == "one":
+        new[:] = 1 if most > R else 0
+        new[R // 2] += most - int(new.sum())
+    indptr = np.concatenate([[0], np.cumsum(new)])
+    if spread == "unordered" and R > 2:
+        indptr[R // 2:] -= indptr[R // 2]
+    new = np.diff(indptr)
+    room = np.maximum(new, 0) + rng.integers(0, 3, R)
+    count = rng.integers(0, 20, R)
+    if R > 2:
+        room[0] = max(int(new[0]) - 1, 0)         # full (if it appends anything)
+        count[1] = -1 if R > 8 else count[1]      # no count of a table: refused
+    start = np.concatenate([[0], np.cumsum(np.maximum(count, 0) + room)])
+    add = rng.integers(0, 1 << 30, total)
+    want, after = np.arange(int(start[-1]) + 1), count.copy()
+    full = False
+    for r in range(R):
+        if new[r] <= 0:
+            continue
+        if count[r] >= 0 and count[r] + new[r] <= start[r + 1] - start[r]:
+            want[start[r] + count[r]:start[r] + count[r] + new[r]] = add[indptr[r]:indptr[r + 1]]
+            after[r] += new[r]
+        else:
+            full = True
+
+    def dev(x):
+        return t.from_numpy(np.asarray(x, dtype=np.int32)).cuda()
+    ip, d_add, d_start = dev(indptr), dev(add), dev(start)
+    for known in (True, False):
+        d_count, d_slots, status = dev(count), dev(np.arange(want.size)), dev([77])
+        if known:
+            B.append_slots(d_start, d_count, d_slots, ip, d_add, status=status)
+        else:
+            assert B.load_library().vtoken_append_slots(
+                R, ip.data_ptr(), d_add.data_ptr(), d_start.data_ptr(), d_count.data_ptr(),
+                d_slots.data_ptr(), status.data_ptr(), t.cuda.current_stream().cuda_stream) == 0
+        t.cuda.synchronize()
+        assert int(status) == (B.STATUS_CODE["VTOKEN_ERR_CAPACITY"] if full else 0)
+        assert np.array_equal(d_count.cpu().numpy(), after)
+        assert np.array_equal(d_slots.cpu().numpy(), want)
 
 
 @pytest.mark.parametrize("R", [256, 257, 600])
