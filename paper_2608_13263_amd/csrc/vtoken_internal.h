@@ -313,15 +313,11 @@ constexpr int64_t decode_max_count(int head_dim, int elem_bytes, int group, int6
 // The smallest split over the element sizes: the workspace bound of the C ABI.
 constexpr int decode_min_split_tokens(int head_dim) { return decode_unit_tokens(head_dim, 2); }
 // Split slots per (request, KV head) in the split launch's grid (where the splits of a head are
-// neighbours). Workgroups are handed to the
-// 8 XCDs in turn, so with an even count and few splits the requests' first splits, which hold
-// the work, fall on the same XCDs (Llama-3-8B Random, 20 splits: one XCD 12% above the mean);
-// rounding a count below 64 up to an odd one spreads them evenly (measured: that call 5%
-// faster). With more splits per request the counts even out by themselves, and the odd count
-// measured 0.2-0.7% slower (Llama-3-70B, 78 splits), so those keep theirs.
-__host__ __device__ constexpr int decode_grid_splits(int splits) {
-  return splits < 64 ? (splits | 1) : splits;
-}
+// neighbours): an odd number. Workgroups are handed to the 8 XCDs in turn, so with an even one the
+// requests' first splits, which hold the work, fall on the same XCDs: 20 slots left one XCD 12%
+// above the mean (Llama-3-8B Random, 5% slower); 64 and 128, under bounds far above the requests,
+// put all of it on one or two (fp8, 8 requests of 2,000 slots, bound 131,072: 110 us, 39 so).
+__host__ __device__ constexpr int decode_grid_splits(int splits) { return splits | 1; }
 
 // (request, split) pairs of the split launch's grid: whole octets, for the kernels that place the
 // heads of a split on one XCD.

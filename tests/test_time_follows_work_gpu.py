@@ -59,3 +59,38 @@ def test_append_of_many_slots(R):
     few, many = _append(R, 4096), _append(129, 4096)
     print(f"[gpu] append {R} x 4096: {few:.1f} us, 129 x 4096: {many:.1f} us", flush=True)
     assert few < 3 * many
+
+
+def _decode(dtype, H, D, G, S, R, count, bounds, layers=8):
+    """us a layer of R requests of `count` slots, under each bound."""
+    t, B = torch(), _B()
+    blocks = -(-count // S) * R
+    g = t.Generator(device="cuda").manual_seed(R + D)
+    kv = t.empty((2 * layers, blocks, S, H, D), dtype=t.float16, device="cuda")
+    kv = kv.normal_(generator=g).to(dtype)
+    cache = B.KVCache(kv, layers, H, D, S)
+    per = -(-count // S) * S
+    slots = _i32((np.arange(R)[:, None] * per + np.arange(count)).ravel())
+    indptr = _i32(np.arange(R + 1) * count)
+    q = t.empty((R, H * G, D), device="cuda").normal_(generator=g)
+    out, times, first = t.empty_like(q), [], None
+    for bound in bounds:
+        ws = t.empty(B.decode_workspace_bytes(R, H * G, D, bound) // 4, device="cuda")
+
+        def call():
+            for layer in range(layers):
+                B.paged_decode(cache, q, indptr, slots, layer, bound, out=out, workspace=ws)
+        times.append(_us(call, 2) / layers)
+        if first is None:
+            first = out.clone()
+        assert float((out - first).norm() / first.norm()) < 1.5e-5
+    return times
+
+
+@pytest.mark.parametrize("G", [1, 8])
+def test_decode_under_a_loose_bound(G):
+    """Bounds 64 times the requests' slots dispatch 64 times the workgroups, but the work in them
+    is the same: all on one XCD, it took seven times as long."""
+    tight, loose = _decode(torch().float8_e4m3fn, 8, 128, G, 32, 8, 2000, [2000, 131072])
+    print(f"[gpu] decode G={G}: {tight:.1f} us, bound 65 times as large {loose:.1f} us", flush=True)
+    assert loose < 4 * tight
