@@ -386,8 +386,9 @@ vtoken_status vtoken_append_slots_n(int32_t num_reqs, int64_t num_new,
  *   out[r][qh] = softmax(scale * q[r][qh] . K[slot]^T) @ V[slot] over the slots of r,
  * K and V being the layer's K and V planes (float32 math; zeros for a request with no slots).
  * Flash-decoding: splits of 1, 2, 4 or 8 times 32 KiB of K per KV head (32768 / (head_dim *
- * elem_bytes) tokens each; chosen from the batch's size and max_tokens), then, where a request
- * may have several, a merge; the workspace
+ * elem_bytes) tokens each; chosen from the batch's size and max_tokens, and shorter where the
+ * requests turn out to hold much less), then, where a request may have several, a merge; the
+ * workspace
  * holds the split partials and is overwritten by every call (calls sharing it must be
  * stream-ordered). A request with more slots than max_tokens provides for is never
  * truncated: its outputs are NaN, unless its slots still fit max_tokens rounded up to a multiple
@@ -398,8 +399,9 @@ vtoken_status vtoken_append_slots_n(int32_t num_reqs, int64_t num_new,
  * slot_indptr[r+1] < slot_indptr[r], or slot_count[r] < 0) reads no slot and gets NaN
  * outputs. The split launch has R * num_kv_heads * ceil(max_tokens / split) workgroups, and
  * those past a request's slots return at once: pass the batch's largest slot count rather
- * than a model's context limit (on MI355X a bound 2, 4 and 8 times too large cost the
- * Llama-3-8B Random decode 2%, 8% and 25%). */
+ * than a model's context limit (on MI355X a bound 2, 4, 8 and 53 times too large cost the
+ * Llama-3-8B Random decode 1%, 7%, 8% and 44%; one of 65 times the slots cost 8 requests of
+ * 2,000 fp8 slots 35%). */
 enum { VTOKEN_KV_FP16 = 0, VTOKEN_KV_BF16 = 1, VTOKEN_KV_FP8_E4M3 = 2 };
 
 typedef struct vtoken_decode {

@@ -455,15 +455,9 @@ vtoken_status paged_decode(const vtoken_cache* cache, const vtoken_decode* d, in
   a.num_slots = cache->num_blocks * cache->block_size;
   a.num_reqs = num_reqs;
   a.max_count = vtoken::decode_max_count(D, cache->elem_bytes, g, d->max_tokens);
-  // (64-bit: max_tokens may lie within one unit of INT32_MAX)
-  const int64_t split =
-      (int64_t)vtoken::decode_unit_tokens(D, cache->elem_bytes) *
-      vtoken::decode_split_units(D, cache->elem_bytes, (int64_t)num_reqs * cache->num_kv_heads,
-                                 d->max_tokens);
-  a.split_tokens = static_cast<int32_t>(split);
-  a.splits = d->max_tokens > 0
-                 ? static_cast<int32_t>(((int64_t)d->max_tokens + split - 1) / split)
-                 : 1;
+  a.split = vtoken::decode_split_rule(D, cache->elem_bytes, num_reqs, cache->num_kv_heads,
+                                      d->max_tokens);
+  a.splits = vtoken::decode_splits(a.split, d->max_tokens);
   const int64_t groups =
       vtoken::decode_grid_groups((int64_t)num_reqs * vtoken::decode_grid_splits(a.splits));
   if (groups * cache->num_kv_heads > INT32_MAX ||

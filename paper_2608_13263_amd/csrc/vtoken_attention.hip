@@ -401,10 +401,11 @@ constexpr int kSplitWaves = kDecodeSplitWaves;
 
 // Split kernel of the paged decode, both products on the matrix cores.
 //
-// kKind: element type; kD: head_dim (32, 64, 128, 256). One workgroup of four waves covers
-// a.split_tokens tokens (a whole number of rounds) of one (request, KV head) and its 1, 2, 4 or 8
-// query heads; in round i wave w takes the kIT tokens from (i * 4 + w) * kIT on, 4 KiB of K and
-// 4 KiB of V (8 KiB each with 512-byte head rows), and computes for them, on the matrix cores
+// kKind: element type; kD: head_dim (32, 64, 128, 256); kShorten: the batch may hold so few slots
+// that its splits are shorter than the host's (decode_split_rule()). One workgroup of four waves covers
+// decode_request_tokens() tokens (a whole number of rounds) of one (request, KV head) and its 1,
+// 2, 4 or 8 query heads; in round i wave w takes the kIT tokens from (i * 4 + w) * kIT on, 4 KiB
+// of K and 4 KiB of V (8 KiB each with 512-byte head rows), and computes for them, on the matrix cores
 // (MFMA 16x16x32, fp16 for fp16 caches, bf16 otherwise; fp8 widened to bf16):
 //   scores  S[token][col] = K_tile (16 x kD) . Q2^T (kD x 16). The float32 query is split into
 //           high and low 16-bit parts (q = hi + lo to ~2^-17; 2^-22 in fp16): column c < 8 of Q2
@@ -443,7 +444,7 @@ constexpr int kSplitWaves = kDecodeSplitWaves;
 // 135 -> 83 us (437 MB).
 // Non-finite K or V values are outside the contract (a zero weight times an infinite value
 // gives NaN).
-template <int kKind, int kD, bool kG8>
+template <int kKind, int kD, bool kG8, bool kShorten>
 __global__ __launch_bounds__(64 * kSplitWaves)
 __attribute__((amdgpu_waves_per_eu(kD * (kKind == 2 ? 1 : 2) > 256 ? 2 : 3)))
 void decode_split_kernel(AttnArgs a) {
@@ -503,19 +504,22 @@ void decode_split_kernel(AttnArgs a) {
     r = blockIdx.x / (gs * H);
   }
   if (r >= a.num_reqs || split >= a.splits) return;
+  const int total = kShorten ? a.slot_indptr[a.num_reqs] - a.slot_indptr[0] : 0;
   const int s0 = a.slot_indptr[r];
   const int c = a.slot_count != nullptr ? a.slot_count[r] : a.slot_indptr[r + 1] - s0;
+  const int st = kShorten ? decode_request_tokens(a.split, c, total) : a.split.tokens;
   const int64_t qh0 = (int64_t)r * a.num_q_heads + h * G;   // first query head's row
-  if (decode_fixed_output(a, s0, c)) {   // written here if there is no merge, else there
+  // (one branch for both, so that all the counts are read together)
+  const bool fixed = decode_fixed_output(a, s0, c);
+  const int t0 = split * st;
+  if (fixed | (t0 >= c)) {
+    if (!fixed || a.splits > 1) return;   // fixed outputs are written here if there is no merge
     const float fill = c == 0 && s0 >= 0 ? 0.f : __builtin_nanf("");
-    if (a.splits > 1) return;
     for (int i = tid; i < G * kD; i += kThreads) a.out[qh0 * kD + i] = fill;
     return;
   }
   // the last split takes what is left (up to a.max_count)
-  const int t0 = split * a.split_tokens;
-  if (t0 >= c) return;
-  const int nt = split + 1 < a.splits && c - t0 > a.split_tokens ? a.split_tokens : c - t0;
+  const int nt = split + 1 < a.splits && c - t0 > st ? st : c - t0;
   const int* slots = a.slots + s0 + t0;
   const uint8_t* kplane = a.kv + (int64_t)(2 * a.layer) * a.plane_bytes;
   const uint8_t* vplane = kplane + a.plane_bytes;
@@ -836,7 +840,7 @@ constexpr int kCombineWaves = 4;
 constexpr int kCombineWavesMany = 16;
 constexpr int kCombineManySplits = 32;   // more splits: 16 waves
 
-template <int kWaves>
+template <int kWaves, bool kShorten>
 __global__ __launch_bounds__(64 * kWaves) void decode_combine_kernel(AttnArgs a) {
   constexpr int kMaxD = 256;
   __shared__ float sum_s[kWaves][kMaxD];
@@ -846,17 +850,19 @@ __global__ __launch_bounds__(64 * kWaves) void decode_combine_kernel(AttnArgs a)
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int total = kShorten ? a.slot_indptr[a.num_reqs] - a.slot_indptr[0] : 0;
   const int s0 = a.slot_indptr[r];
   const int c = a.slot_count != nullptr ? a.slot_count[r] : a.slot_indptr[r + 1] - s0;
+  const int st = kShorten ? decode_request_tokens(a.split, c, total) : a.split.tokens;
   const int D = a.head_dim;
   const int64_t rs = D + 2;  // record stride
   float* out = a.out + ((int64_t)r * a.num_q_heads + qh) * D;
-  if (decode_fixed_output(a, s0, c)) {
+  const int ns = min(static_cast<int>(((int64_t)c + st - 1) / st), a.splits);
+  if (decode_fixed_output(a, s0, c) | (ns < 1)) {
     const float fill = c == 0 && s0 >= 0 ? 0.f : __builtin_nanf("");
     for (int d = tid; d < D; d += 64 * kWaves) out[d] = fill;
     return;
   }
-  const int ns = min(static_cast<int>(((int64_t)c + a.split_tokens - 1) / a.split_tokens), a.splits);
   const float* rec0 = a.workspace + ((int64_t)r * a.num_q_heads + qh) * a.splits * rs;
   // A record's values: float pairs (its start and its stride are even), pair lane and lane + 64
   const int p0 = lane * 2, p1 = 128 + lane * 2;
@@ -927,29 +933,45 @@ __global__ __launch_bounds__(64 * kWaves) void decode_combine_kernel(AttnArgs a)
   }
 }
 
-template <int kKind, int kD>
+template <int kKind, int kD, bool kShorten>
 auto split_kernel(bool g8) -> void (*)(AttnArgs) {
   if constexpr (kKind == 0) {
-    return decode_split_kernel<kKind, kD, false>;   // one kernel for all groups
+    return decode_split_kernel<kKind, kD, false, kShorten>;   // one kernel for all groups
   } else {
-    return g8 ? decode_split_kernel<kKind, kD, true> : decode_split_kernel<kKind, kD, false>;
+    return g8 ? decode_split_kernel<kKind, kD, true, kShorten>
+              : decode_split_kernel<kKind, kD, false, kShorten>;
   }
+}
+
+template <int kKind, int kD>
+auto pick_split(const AttnArgs& a) -> void (*)(AttnArgs) {
+  const bool g8 = kKind != 0 && a.num_q_heads == 8 * a.num_kv_heads;
+  return a.split.few > 0 ? split_kernel<kKind, kD, true>(g8) : split_kernel<kKind, kD, false>(g8);
 }
 
 template <int kKind>
 hipError_t launch_split(const AttnArgs& a, hipStream_t stream) {
   const int64_t groups = decode_grid_groups((int64_t)a.num_reqs * decode_grid_splits(a.splits));
   const dim3 grid(static_cast<unsigned>(groups * a.num_kv_heads));
-  const bool g8 = kKind != 0 && a.num_q_heads == 8 * a.num_kv_heads;
   void (*kernel)(AttnArgs) = nullptr;
   switch (a.head_dim) {
-    case 32: kernel = split_kernel<kKind, 32>(g8); break;
-    case 64: kernel = split_kernel<kKind, 64>(g8); break;
-    case 128: kernel = split_kernel<kKind, 128>(g8); break;
-    case 256: kernel = split_kernel<kKind, 256>(g8); break;
+    case 32: kernel = pick_split<kKind, 32>(a); break;
+    case 64: kernel = pick_split<kKind, 64>(a); break;
+    case 128: kernel = pick_split<kKind, 128>(a); break;
+    case 256: kernel = pick_split<kKind, 256>(a); break;
     default: return hipErrorInvalidValue;
   }
   hipLaunchKernelGGL(kernel, grid, dim3(64 * kSplitWaves), 0, stream, a);
+  return hipGetLastError();
+}
+
+template <bool kShorten>
+hipError_t launch_combine(const AttnArgs& a, hipStream_t stream) {
+  const bool many = a.splits > kCombineManySplits;
+  const auto kernel = many ? decode_combine_kernel<kCombineWavesMany, kShorten>
+                           : decode_combine_kernel<kCombineWaves, kShorten>;
+  hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>((int64_t)a.num_reqs * a.num_q_heads)),
+                     dim3(64 * (many ? kCombineWavesMany : kCombineWaves)), 0, stream, a);
   return hipGetLastError();
 }
 
@@ -983,7 +1005,7 @@ hipError_t launch_slot_mapping(const SlotMapArgs& a, hipStream_t stream) {
 hipError_t launch_paged_decode(const AttnArgs& a, hipStream_t stream) {
   if (a.num_reqs <= 0) return hipSuccess;
   const int round = decode_round_tokens(a.head_dim, a.kv_kind == 2 ? 1 : 2);
-  if (a.split_tokens <= 0 || a.split_tokens % round != 0) return hipErrorInvalidValue;
+  if (a.split.tokens <= 0 || a.split.tokens % round != 0) return hipErrorInvalidValue;
   hipError_t e;
   switch (a.kv_kind) {
     case 0: e = launch_split<0>(a, stream); break;
@@ -994,13 +1016,7 @@ hipError_t launch_paged_decode(const AttnArgs& a, hipStream_t stream) {
   // a single split has written the outputs
   if (a.splits == 1) return e;
   if (e != hipSuccess) return e;
-  const bool many = a.splits > kCombineManySplits;
-  const int waves = many ? kCombineWavesMany : kCombineWaves;
-  hipLaunchKernelGGL(many ? decode_combine_kernel<kCombineWavesMany>
-                          : decode_combine_kernel<kCombineWaves>,
-                     dim3(static_cast<unsigned>((int64_t)a.num_reqs * a.num_q_heads)),
-                     dim3(64 * waves), 0, stream, a);
-  return hipGetLastError();
+  return a.split.few > 0 ? launch_combine<true>(a, stream) : launch_combine<false>(a, stream);
 }
 
 // Split partials of vtoken_paged_decode_noalloc: a library-held workspace for callers that

@@ -183,6 +183,14 @@ struct AppendArgs {
   int32_t* status;
 };
 
+// How long the splits of a decode are (decode_split_rule()).
+struct DecodeSplit {
+  int32_t tokens;   // of a split in a batch whose requests are as long as the bound: a multiple of
+                    // decode_round_tokens(), as are its halves below
+  int32_t few;      // slots of a batch below which such splits leave the chip idle (0: none)
+  int32_t room[3];  // slots of a request for which there is room at a half, a quarter, an eighth
+};
+
 // Paged decode attention of one layer through a slot mapping.
 struct AttnArgs {
   const uint8_t* kv;
@@ -196,7 +204,7 @@ struct AttnArgs {
   int32_t num_slots;
   int32_t num_reqs;
   int32_t splits;    // split records per (request, query head) in the workspace
-  int32_t split_tokens;  // tokens per split: a multiple of decode_round_tokens()
+  DecodeSplit split;
   int64_t max_count;     // slots a request may hold (more: NaN outputs)
   float scale;
   const float* q;
@@ -274,7 +282,7 @@ constexpr int decode_round_tokens(int head_dim, int elem_bytes) {
 constexpr int decode_unit_tokens(int head_dim, int elem_bytes) {
   return 32768 / (head_dim * elem_bytes);
 }
-// Units per split for `pairs` (request, KV head) pairs of at most max_tokens slots. Short splits
+// Units per split for `pairs` (request, KV head) pairs of max_tokens slots each. Short splits
 // pay the start of a workgroup (3 dependent reads, the query operands) and its record often, long
 // ones leave the chip part idle at the end: the time is estimated as the workgroups' rounds
 // through the chip plus half a workgroup's time, with a start of 3 us and a unit's 64 KiB of K
@@ -302,6 +310,53 @@ constexpr int decode_split_units(int head_dim, int elem_bytes, int64_t pairs,
   }
   return best;
 }
+
+// Workgroups of a split launch below which shorter splits are faster.
+constexpr int kDecodeFewGroups = 384;   // 1.5 per CU
+
+// The host knows the bound max_tokens, not the requests' slots, and takes units and room for splits
+// as if every request were that long. Where the batch holds so much less that splits of this
+// length would be fewer than kDecodeFewGroups workgroups, the kernels take shorter ones, as far as
+// the room goes. That needs fewer (request, KV head) pairs than workgroups; other calls keep the
+// kernels that don't look at the batch's slots (those are 0.2 us a kernel slower, 1% of 128 requests
+// of 1,000 slots). Per layer with the host's and with halved splits: fp8, 8 requests of 2,000 slots,
+// 8 heads x 128, bound 8,000 19.4 us (250 workgroups), 15.7 (500); bf16, 8 of 1,024, bound 4,096
+// 15.4 (256), 13.0 (512); bf16, 16 of 1,500, 8 x 32, bound 12,000 19.1 (187), 15.1 (375); but
+// bf16, 32 of 4,000, 1 x 128, bound 16,000 19.4 (500), 20.8 (1,000); bf16, 6 of 3,000, 4 x 256,
+// bound 12,000 21.7 (562), 23.0 (1,125).
+constexpr DecodeSplit decode_split_rule(int head_dim, int elem_bytes, int64_t num_reqs,
+                                        int64_t heads, int64_t max_tokens) {
+  const int64_t unit = decode_unit_tokens(head_dim, elem_bytes);
+  const int units = decode_split_units(head_dim, elem_bytes, num_reqs * heads, max_tokens);
+  const int64_t splits = max_tokens > 0 ? (max_tokens + units * unit - 1) / (units * unit) : 1;
+  const bool shorten = units > 1 && num_reqs * heads < kDecodeFewGroups;
+  DecodeSplit s{static_cast<int32_t>(units * unit),
+                static_cast<int32_t>(shorten ? kDecodeFewGroups * units * unit / heads : 0),
+                {-1, -1, -1}};
+  for (int k = 0; k < 3 && (units >> (k + 1)) > 0; ++k) {
+    const int64_t room = (units >> (k + 1)) * unit * splits;
+    s.room[k] = static_cast<int32_t>(room < INT32_MAX ? room : INT32_MAX);
+  }
+  return s;
+}
+
+// Split slots of a request as long as the bound.
+constexpr int32_t decode_splits(const DecodeSplit& s, int64_t max_tokens) {
+  return max_tokens > 0 ? static_cast<int32_t>((max_tokens + s.tokens - 1) / s.tokens) : 1;
+}
+
+// Tokens per split of a request of `count` slots in a batch of `total`: its splits fit the room, or
+// they are as long as the host's (the last one then takes what is left). A smaller total and a
+// smaller room imply the larger ones, so the halvings add up (no branches: the kernels wait for
+// this before their first load of K).
+__host__ __device__ constexpr int decode_request_tokens(const DecodeSplit& s, int count,
+                                                        int total) {
+  const int halvings = ((total < s.few) & (count <= s.room[0])) +
+                       ((total < s.few >> 1) & (count <= s.room[1])) +
+                       ((total < s.few >> 2) & (count <= s.room[2]));
+  return s.tokens >> halvings;
+}
+
 // The most slots a request may hold: max_tokens rounded up to whole units of the size below (at
 // least one), which is what the C ABI has promised since splits had that size.
 constexpr int64_t decode_max_count(int head_dim, int elem_bytes, int group, int64_t max_tokens) {

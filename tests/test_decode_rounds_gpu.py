@@ -30,6 +30,14 @@ def _reference(kv, q, slots, H, D):
     ("bf16", 1, 256, 8, [200, 128, 100], 130),                   # past max_tokens, within its units
     ("bf16", 1, 64, 1, [40000, 9], 0),                           # merge of over 64 records
     ("fp16", 1, 256, 1, [9000, 4200], 0),
+    # bounds far above: splits a half, a quarter, an eighth of the host's, where there is room
+    ("fp8", 8, 128, 8, [2000, 255, 257, 1], 8000),
+    ("fp8", 8, 128, 8, [2000, 257, 0], 131072),
+    ("bf16", 8, 128, 1, [1024, 4097, 129], 60000),
+    ("fp16", 2, 256, 2, [900, 64, 65], 131072),
+    ("bf16", 8, 32, 4, [1500, 513], 131072),
+    ("fp8", 4, 64, 2, [1500, 4097], 30000),
+    ("bf16", 8, 128, 4, [16000, 40, 700], 60000),
 ])
 def test_decode_rounds(dtype, H, D, G, counts, bound):
     """Against float64; scores rise along every request, so that the running maximum moves in each
@@ -50,6 +58,9 @@ def test_decode_rounds(dtype, H, D, G, counts, bound):
                          perm.to(torch.int32).cuda(), 0, bound or max(counts)).cpu().double()
     host = kv.float()
     for r, n in enumerate(counts):
+        if n == 0:
+            assert (out[r] == 0).all()
+            continue
         ref = _reference(host, q[r], slice(int(indptr[r]), int(indptr[r]) + n), H, D)
         scale = float(ref.pow(2).mean().sqrt())
         assert float((out[r] - ref).norm() / ref.norm()) < 1.5e-5, (r, n)

@@ -89,8 +89,9 @@ def _decode(dtype, H, D, G, S, R, count, bounds, layers=8):
 
 @pytest.mark.parametrize("G", [1, 8])
 def test_decode_under_a_loose_bound(G):
-    """Bounds 64 times the requests' slots dispatch 64 times the workgroups, but the work in them
-    is the same: all on one XCD, it took seven times as long."""
+    """Bounds 65 times the requests' slots dispatch up to 65 times the workgroups, but the work in
+    them is the same: all on one XCD it took seven times as long, in splits as long as the bound
+    asks for (one workgroup a head) 2.4 times."""
     tight, loose = _decode(torch().float8_e4m3fn, 8, 128, G, 32, 8, 2000, [2000, 131072])
     print(f"[gpu] decode G={G}: {tight:.1f} us, bound 65 times as large {loose:.1f} us", flush=True)
-    assert loose < 4 * tight
+    assert loose < 1.9 * tight
