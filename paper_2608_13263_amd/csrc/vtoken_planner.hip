@@ -122,38 +122,51 @@ __device__ __forceinline__ void pl_count_refs(const PlannerArgs& a, int64_t thre
   }
 }
 
-// One bit per live slot of tokens [from, to), by waves `wave` of `waves`. Tokens go 64 to a
-// wave: the bits of the wave's tokens that fall in one block are ORed across the wave and set
-// with one atomic (up to 8 blocks per wave; a wave's remaining tokens set their bits one by one).
-template <bool kPow2>
+// One bit per live slot of tokens [from, to), by waves `wave` of `waves`, kGroups times 64 tokens of
+// a wave in flight. The bits of 64 tokens that fall in one block are ORed across the wave and set
+// with one atomic (up to 8 blocks per 64 tokens; the remaining tokens set their bits one by one).
+template <bool kPow2, int kGroups = 1>
 __device__ __forceinline__ void pl_count_waves(const PlannerArgs& a, int64_t from, int64_t to,
                                                int64_t wave, int64_t waves) {
   const BlockDiv<kPow2> bd(a.block_size);
   const int lane = threadIdx.x & 63;
-  for (int64_t w0 = from + wave * 64; w0 < to; w0 += waves * 64) {
-    const int64_t t = w0 + lane;
-    const bool lv = t < to && a.live[t] != 0;
-    const int s = lv ? a.slot_in[t] : -1;
-    const bool bad = lv && (s < 0 || s >= a.num_slots);
-    if (bad) pl_error(a.counters, VTOKEN_ERR_SLOT);
-    const bool ok = lv && !bad;
-    const int blk = ok ? bd.div(s) : -1;
-    const int off = ok ? bd.mod(s) : 0;
-    uint64_t pending = __ballot(ok);
-    for (int it = 0; it < 8 && pending != 0; ++it) {
-      const int leader = __builtin_ctzll(pending);
-      const int lb = __builtin_amdgcn_readlane(blk, leader);
-      const bool mine = ok && blk == lb;
-      const uint32_t lo = wave_or(mine && off < 32 ? 1u << off : 0u);
-      const uint32_t hi = wave_or(mine && off >= 32 ? 1u << (off - 32) : 0u);
-      if (lane == leader) {
-        atomicOr(reinterpret_cast<unsigned long long*>(&a.live_bits[lb]),
-                 (static_cast<unsigned long long>(hi) << 32) | lo);
-      }
-      pending &= ~__ballot(mine);
+  for (int64_t w0 = from + wave * 64 * kGroups; w0 < to; w0 += waves * 64 * kGroups) {
+    bool lv[kGroups];
+    int sl[kGroups];
+#pragma unroll
+    for (int q = 0; q < kGroups; ++q) {
+      const int64_t t = w0 + q * 64 + lane;
+      lv[q] = t < to && a.live[t] != 0;
     }
-    if ((pending >> lane) & 1) {
-      atomicOr(reinterpret_cast<unsigned long long*>(&a.live_bits[blk]), 1ull << off);
+#pragma unroll
+    for (int q = 0; q < kGroups; ++q) sl[q] = lv[q] ? a.slot_in[w0 + q * 64 + lane] : -1;
+#pragma unroll
+    for (int q = 0; q < kGroups; ++q) {
+      const int s = sl[q];
+      const bool bad = lv[q] && (s < 0 || s >= a.num_slots);
+      if (bad) pl_error(a.counters, VTOKEN_ERR_SLOT);
+      const bool ok = lv[q] && !bad;
+      const int blk = ok ? bd.div(s) : -1;
+      const int off = ok ? bd.mod(s) : 0;
+      uint64_t pending = __ballot(ok);
+      const int live = __popcll(pending);
+      for (int it = 0; it < 8 && pending != 0; ++it) {
+        const int leader = __builtin_ctzll(pending);
+        const int lb = __builtin_amdgcn_readlane(blk, leader);
+        const bool mine = ok && blk == lb;
+        const uint32_t lo = wave_or(mine && off < 32 ? 1u << off : 0u);
+        const uint32_t hi = wave_or(mine && off >= 32 ? 1u << (off - 32) : 0u);
+        if (lane == leader) {
+          atomicOr(reinterpret_cast<unsigned long long*>(&a.live_bits[lb]),
+                   (static_cast<unsigned long long>(hi) << 32) | lo);
+        }
+        pending &= ~__ballot(mine);
+        // tokens spread over the blocks: no use looking for neighbours
+        if (it == 1 && __popcll(pending) + 2 >= live) break;
+      }
+      if ((pending >> lane) & 1) {
+        atomicOr(reinterpret_cast<unsigned long long*>(&a.live_bits[blk]), 1ull << off);
+      }
     }
   }
 }
@@ -166,50 +179,97 @@ __global__ __launch_bounds__(256) void pl_count_kernel(PlannerArgs a) {
   pl_count_waves<kPow2>(a, 0, a.num_tokens, thread / 64, threads / 64);
 }
 
-// The same for requests of many tokens: workgroup (r, y) takes every gridDim.y-th tile of
-// request r's tokens and collects their bits in LDS, one bitmap per entry of the request's table,
-// then sets each block's bits with one atomic. Earlier passes leave a request's tokens spread
-// over its blocks, so that nearly every token of a wave lies in another block, and one atomic
-// per token was the time of the launch: half of 256 requests of 2-8K tokens in permuted order,
-// S = 16, 34.5 us, 13.7 so. n_b[b], which the next launch fills, holds the block's entry
-// meanwhile; what is read there may be another request's (a shared block) or anything (a block of
-// no table), so an entry counts only if the request's table has the block there, and the token's
-// bit is set by itself otherwise. Tables of more than kPlCountBlocks entries take the way of the
-// launch above.
+// The same for requests of many tokens: workgroup y of request r takes every split-th tile of the
+// request's tokens and collects their bits in LDS, one bitmap per entry of the request's table, then
+// sets each block's bits with one atomic. Earlier passes leave a request's tokens spread over its
+// blocks, so that nearly every token of a wave lies in another block, and one atomic per token was
+// the time of the launch: half of 256 requests of 2-8K tokens in permuted order, S = 16, 34.5 us,
+// 13.7 so. n_b[b], which the next launch fills, holds the block's entry meanwhile; what is read
+// there may be another request's (a shared block) or anything (a block of no table), so an entry
+// counts only if the request's table has the block there, and the token's bit is set by itself
+// otherwise. Tables of more than kPlCountBlocks entries take the way of the launch above.
+//
+// split follows from the mean length, the only one the host knows. A request's own workgroups take
+// kPlCountTiles tiles each; what is left of a longer request goes the way of the launch above, by
+// further workgroups, each of which looks at one piece of the token axis (0.1-0.8 us where there is
+// nothing left): a request of 600K tokens among 511 of 100, left to one workgroup, took 2,146 us, 369
+// so (the whole planning).
 constexpr int kPlCountThreads = 512;
+constexpr int kPlCountWaves = kPlCountThreads / 64;
 constexpr int kPlCountBlocks = 2048;
 constexpr int kPlCountTokens = 8;                                  // per thread and tile
 constexpr int kPlCountTile = kPlCountThreads * kPlCountTokens;     // 4096
+constexpr int kPlCountTiles = 2;
+constexpr int kPlCountRest = kPlCountTiles * kPlCountTile;   // tokens of a further workgroup
 constexpr int kPlCountGrid = 512;   // workgroups wanted
 constexpr int kPlCountMinTokens = 1 << 19;
 
+// The request that token t belongs to (the number of requests that end at or before it, at most the
+// last one), by all threads: 512 probes at a time.
+__device__ __forceinline__ int pl_request_of(const PlannerArgs& a, int t) {
+  __shared__ int below_s[2][kPlCountWaves];
+  const int tid = threadIdx.x;
+  int lo = 0, len = a.num_reqs;
+  for (int round = 0; len > 0; ++round) {
+    const int step = (len + kPlCountThreads - 1) / kPlCountThreads;
+    const int64_t i = (int64_t)(tid + 1) * step - 1;
+    const uint64_t m = __ballot(i < len && a.tok_indptr[lo + (i < len ? i : 0) + 1] <= t);
+    if ((tid & 63) == 0) below_s[round & 1][tid >> 6] = __popcll(m);
+    __syncthreads();   // (the rounds alternate between two arrays)
+    int k = 0;
+#pragma unroll
+    for (int w = 0; w < kPlCountWaves; ++w) k += below_s[round & 1][w];
+    lo += k * step;
+    len = max(0, min(step - 1, len - k * step));
+  }
+  return __builtin_amdgcn_readfirstlane(min(lo, a.num_reqs - 1));
+}
+
 template <bool kPow2>
-__global__ __launch_bounds__(kPlCountThreads) void pl_count_request_kernel(PlannerArgs a) {
+__global__ __launch_bounds__(kPlCountThreads) void pl_count_request_kernel(PlannerArgs a,
+                                                                           int split) {
   __shared__ int ids_s[kPlCountBlocks];
   __shared__ uint32_t bits_s[kPlCountBlocks][2];
-  constexpr int kWaves = kPlCountThreads / 64;
   const BlockDiv<kPow2> bd(a.block_size);
   const int tid = threadIdx.x;
-  const int r = blockIdx.x;
-  const int wg = blockIdx.y * gridDim.x + blockIdx.x;
-  pl_count_refs(a, (int64_t)wg * kPlCountThreads + tid,
-                (int64_t)gridDim.x * gridDim.y * kPlCountThreads);
-  const int t0 = a.tok_indptr[r], t1 = a.tok_indptr[r + 1];
+  const int wave = tid / 64;
+  const int64_t own = (int64_t)split * kPlCountTiles * kPlCountTile;   // tokens
+  pl_count_refs(a, (int64_t)blockIdx.x * kPlCountThreads + tid,
+                (int64_t)gridDim.x * kPlCountThreads);
+  const int64_t tile = (int64_t)blockIdx.x - (int64_t)a.num_reqs * split;
+  if (tile >= 0) {   // what requests longer than their own workgroups take have in this tile
+    const int from = static_cast<int>(tile * kPlCountRest);
+    const int to = static_cast<int>(min((int64_t)from + kPlCountRest, (int64_t)a.num_tokens));
+    // (requests that begin and end within the tile are none)
+    const int r0 = pl_request_of(a, from);
+    const int64_t rest0 = max((int64_t)a.tok_indptr[r0] + own, (int64_t)from);
+    const int end0 = min(a.tok_indptr[r0 + 1], to);
+    if (rest0 < end0) {
+      pl_count_waves<kPow2, kPlCountTokens>(a, rest0, end0, wave, kPlCountWaves);
+    }
+    return;
+  }
+  const int r = blockIdx.x % a.num_reqs;
+  const int y = blockIdx.x / a.num_reqs;
+  // (a range outside the tokens, reported by the next launch, is cut to them)
+  const int first = a.tok_indptr[r], last = a.tok_indptr[r + 1];
+  const int t0 = max(first, 0), t1 = min(last, a.num_tokens);
   const int b0 = a.bt_indptr[r], b1 = a.bt_indptr[r + 1];
-  if (blockIdx.y == 0) {   // tokens of no request (the flat count takes them too)
+  if (y == 0) {   // tokens of no request (the flat count takes them too)
     if (r == 0) {
-      pl_count_waves<kPow2>(a, 0, min(t0, a.num_tokens), tid / 64, kWaves);
+      pl_count_waves<kPow2, kPlCountTokens>(a, 0, min(first, a.num_tokens), wave, kPlCountWaves);
     }
     if (r == a.num_reqs - 1) {
-      pl_count_waves<kPow2>(a, max(t1, 0), a.num_tokens, tid / 64, kWaves);
+      pl_count_waves<kPow2, kPlCountTokens>(a, max(last, 0), a.num_tokens, wave,
+                                            kPlCountWaves);
     }
   }
-  // (a malformed range is reported by the next launch)
-  if (t0 < 0 || t1 < t0 || t1 > a.num_tokens) return;
-  const int n = t1 - t0;
+  if (t1 <= t0) return;
+  const int n = static_cast<int>(min((int64_t)t1 - t0, own));
   const int m = b1 - b0;
   if (b0 < 0 || m < 0 || b1 > a.num_bt_entries || m > kPlCountBlocks) {
-    pl_count_waves<kPow2>(a, t0, t1, blockIdx.y * kWaves + tid / 64, (int64_t)gridDim.y * kWaves);
+    pl_count_waves<kPow2, kPlCountTokens>(a, t0, t0 + n, y * kPlCountWaves + wave,
+                                          (int64_t)split * kPlCountWaves);
     return;
   }
   for (int j = tid; j < m; j += kPlCountThreads) {
@@ -221,7 +281,7 @@ __global__ __launch_bounds__(kPlCountThreads) void pl_count_request_kernel(Plann
     if (in) a.n_b[b] = j;
   }
   __syncthreads();
-  for (int base = blockIdx.y * kPlCountTile; base < n; base += gridDim.y * kPlCountTile) {
+  for (int base = y * kPlCountTile; base < n; base += split * kPlCountTile) {
     uint8_t lv[kPlCountTokens];
     int sl[kPlCountTokens], at[kPlCountTokens];
 #pragma unroll
@@ -665,9 +725,13 @@ hipError_t launch_planner(const PlannerArgs& a, hipStream_t stream) {
     int64_t split = (kPlCountGrid + a.num_reqs - 1) / a.num_reqs;
     const int64_t tiles = (mean + kPlCountTile - 1) / kPlCountTile;
     split = split < tiles ? split : tiles;
+    // (no request can be longer than its own workgroups take: none for the rest)
+    const int64_t rest = split * kPlCountTiles * kPlCountTile < a.num_tokens
+                             ? ((int64_t)a.num_tokens + kPlCountRest - 1) / kPlCountRest
+                             : 0;
     hipLaunchKernelGGL(pow2 ? pl_count_request_kernel<true> : pl_count_request_kernel<false>,
-                       dim3(a.num_reqs, static_cast<unsigned>(split)), dim3(kPlCountThreads), 0,
-                       stream, a);
+                       dim3(static_cast<unsigned>(a.num_reqs * split + rest)),
+                       dim3(kPlCountThreads), 0, stream, a, static_cast<int>(split));
   } else {
     hipLaunchKernelGGL(pow2 ? pl_count_kernel<true> : pl_count_kernel<false>,
                        dim3(grid_for((int64_t)a.num_bt_entries + a.num_tokens)), dim3(256), 0,

@@ -179,3 +179,68 @@ def test_partial_count_by_request(S, reqs, lens, shared):
                                prefix_tokens=256 if shared else 0)
     assert inp.num_tokens >= 1 << 19
     partial_parity(inp, label=f"count by request S={S}")
+
+
+def _mixed(lens, S, seed):
+    """Ragged batch whose every second request holds its tokens in permuted order, half live."""
+    rng = np.random.default_rng(seed)
+    masks = [(rng.random(n) < 0.5).astype(np.uint8) for n in lens]
+    inp = W.from_masks(masks, W.KVShape(1, 1, 8, S, "fp16"), free_blocks=4000, seed=seed)
+    slots = []
+    for r, n in enumerate(lens):
+        ids = inp.block_ids[inp.bt_indptr[r]:inp.bt_indptr[r + 1]].astype(np.int64)
+        p = np.arange(n)
+        s = ids[p // S] * S + p % S
+        slots.append(rng.permutation(s) if r % 2 else s)
+    inp.slot_in = np.concatenate(slots).astype(np.int32)
+    return inp
+
+
+@pytest.mark.parametrize("lens", [
+    [600000] + [100] * 400,              # one long request first, in the middle, last, alone
+    [100] * 200 + [600000] + [90] * 200,
+    [80] * 400 + [600001],
+    [530000],
+    [8192] * 20 + [8193, 30000, 16385] + [5000] * 66,   # just what a request's own workgroups take
+    [1] * 300 + [400000, 1, 1, 200000, 3] + [50] * 200,
+    [1000] * 520 + [0] * 5 + [90000],                   # more requests than probes of one round
+], ids=lambda x: f"{len(x)}x{max(x)}")
+def test_partial_count_of_uneven_requests(lens):
+    """At least 2^19 tokens and a mean of 1,024, in requests far longer than the mean."""
+    inp = _mixed(lens, 16, len(lens))
+    assert inp.num_tokens >= 1 << 19 and inp.num_tokens // inp.num_reqs >= 1024
+    partial_parity(inp, label=f"uneven R={len(lens)}")
+
+
+@pytest.mark.parametrize("where", ["own", "rest", "after", "none"])
+@pytest.mark.parametrize("cut", [False, True])
+def test_partial_count_reports_slots_outside_the_pool(where, cut):
+    """A live token's slot past the pool is reported wherever the count finds it - among the tokens
+    of a request's own workgroups, in the rest of a long one, past the last request's - and before
+    a request's malformed range (cut: the last one ends past the tokens)."""
+    t, B = torch(), _B()
+    inp = _mixed([600000] + [100] * 300, 16, 5)
+    T = inp.num_tokens
+    tok = inp.tok_indptr.copy()
+    if where == "after":
+        tok[-1] -= 1   # (the last token belongs to no request)
+        tok[-2] -= 1
+    if cut:
+        tok[-1] = T + 5
+        inp.live[T - 1] = 1
+    at = {"own": 3, "rest": 590000, "after": T - 1, "none": 0}[where]
+    slots = inp.slot_in.copy()
+    if where != "none":
+        inp.live[at] = 1
+        slots[at] = inp.num_blocks * 16
+    cache = B.KVCache(W.kv_device(inp.shape, inp.num_blocks, 1), 1, 1, 8, 16)
+    batch = B.Batch.from_inputs(inp)
+    batch.tok_indptr = t.from_numpy(tok).cuda()
+    plan, state = B.Plan.allocate(batch, 16), B.PlannerState.allocate(inp.num_blocks, batch)
+    B.plan_partial(cache, batch, t.from_numpy(slots).cuda(), plan, state)
+    t.cuda.synchronize()
+    got = int(plan.counters[3])
+    if where != "none":
+        assert got == B.STATUS_CODE["VTOKEN_ERR_SLOT"]
+    else:
+        assert got == (B.STATUS_CODE["VTOKEN_ERR_TOK_LEN"] if cut else 0)

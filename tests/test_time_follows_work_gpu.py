@@ -95,3 +95,36 @@ def test_decode_under_a_loose_bound(G):
     tight, loose = _decode(torch().float8_e4m3fn, 8, 128, G, 32, 8, 2000, [2000, 131072])
     print(f"[gpu] decode G={G}: {tight:.1f} us, bound 65 times as large {loose:.1f} us", flush=True)
     assert loose < 1.9 * tight
+
+
+def _plan_partial(lens, S=16):
+    """us of the partial pass's planning: 85% live, one request in two in permuted order."""
+    t, B = torch(), _B()
+    rng = np.random.default_rng(len(lens))
+    blocks = -(-np.asarray(lens) // S)
+    M = int(blocks.sum())
+    perm = rng.permutation(M + 4000)
+    at = np.concatenate([[0], np.cumsum(blocks)])
+    slots = []
+    for r, n in enumerate(lens):
+        s = perm[at[r] + np.arange(n) // S] * S + np.arange(n) % S
+        slots.append(rng.permutation(s) if r % 2 else s)
+    T = int(np.sum(lens))
+    kv = t.zeros((2, perm.size, S, 1, 8), dtype=t.float16, device="cuda")
+    live = t.from_numpy((rng.random(T) < 0.85).astype(np.uint8)).cuda()
+    batch = B.Batch(_i32(lens), _i32(np.concatenate([[0], np.cumsum(lens)])), _i32(at),
+                    _i32(perm[:M]), live, _i32(perm[M:]))
+    cache = B.KVCache(kv, 1, 1, 8, S)
+    plan, state = B.Plan.allocate(batch, S), B.PlannerState.allocate(perm.size, batch)
+    slot_in = _i32(np.concatenate(slots))
+    us = _us(lambda: B.plan_partial(cache, batch, slot_in, plan, state), 4)
+    assert int(plan.counters[3]) == 0
+    return us
+
+
+def test_partial_planning_of_a_long_request_among_short_ones():
+    """One request of 600K tokens, alone and with 511 of 100 beside it: the same planning but for
+    the short ones' (left to a single workgroup it took six times as long)."""
+    alone, among = _plan_partial([600000]), _plan_partial([600000] + [100] * 511)
+    print(f"[gpu] plan_partial 1 x 600K: {alone:.0f} us, among 511 x 100: {among:.0f} us", flush=True)
+    assert among < 2.5 * alone
