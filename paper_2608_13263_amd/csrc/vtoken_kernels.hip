@@ -42,11 +42,17 @@ static_assert(kPlanThreadsSplit % 64 == 0 && kPlanThreadsSplit <= kPlanThreads,
 // error code as its live count, which the plan kernel picks up.
 // ------------------------------------------------------------------------------------------
 //
-// kCheckFree (admit_kernel follows): workgroup r also looks over the r-th share of the free list
-// and leaves the first entry outside the pool in admitted[r] (INT_MAX: none), which the admission
-// reads before it writes its flags. The one workgroup of the admission spent 13 of its 18.7 us on
-// the 170K consumed entries of a batch of 1,024 requests and 5.2M tokens; shared out they cost
-// the count launch 1 us (plan and mapping of that batch 50 -> 37 us).
+// kCheckFree (admit_kernel<true> follows): the workgroups also look over the free list, a share
+// each, as far as a pass can use it (destinations are fewer than table entries), and leave the first
+// entry outside the pool that they found in admitted[r] (INT_MAX: none), which the admission reads
+// before it writes its flags. The one workgroup of the admission spent 13 of its 18.7 us on the 170K
+// consumed entries of a batch of 1,024 requests and 5.2M tokens; shared out they cost the count
+// launch 1 us (plan and mapping of that batch 50 -> 37 us). It pays from kCheckFreeEntries usable
+// entries on: below, the admission's rounds of 8,192 cost less than the barriers here (4,096
+// requests of 50 tokens, 16,384 entries: 27.9 and 28.7 us), and the whole list instead of its usable
+// part cost 257 requests of 20 tokens with 3M free blocks 24.2 us for 11.7.
+constexpr int kCheckFreeEntries = 32768;
+
 template <int kThreads, bool kCheckFree>
 __global__ __launch_bounds__(kThreads) void count_kernel(MetaArgs a) {
   __shared__ int wave_sum[kThreads / 64];
@@ -55,10 +61,11 @@ __global__ __launch_bounds__(kThreads) void count_kernel(MetaArgs a) {
   const int tid = threadIdx.x;
   const int S = a.block_size;
   if constexpr (kCheckFree) {
+    const int64_t usable = min(a.free_len, a.num_bt_entries);
+    const int64_t share = (usable + a.num_reqs - 1) / a.num_reqs;
+    const int64_t j1 = min((r + 1) * share, usable);
     if (tid == 0) first_bad = INT_MAX;
     __syncthreads();
-    const int64_t share = ((int64_t)a.free_len + a.num_reqs - 1) / a.num_reqs;
-    const int64_t j1 = min((r + 1) * share, (int64_t)a.free_len);
     for (int64_t j = r * share + tid; j < j1; j += kThreads) {
       const int blk = a.free_list[j];
       if (blk < 0 || blk >= a.num_blocks) atomicMin(&first_bad, static_cast<int>(j));
@@ -224,7 +231,7 @@ __device__ __forceinline__ int admission_status(const MetaArgs& a, const Admissi
   }
   if (!report) return status;
   if (first_bad != nullptr) {
-    if (status == 0 && !a.inplace && *first_bad < adm.used) status = VTOKEN_ERR_BLOCK_RANGE;
+    if (status == 0 && *first_bad < adm.used) status = VTOKEN_ERR_BLOCK_RANGE;
   } else if (status == 0 && !a.inplace) {
     // every consumed free-list entry must be a block of the pool (eight loads in flight per
     // thread)
@@ -268,6 +275,7 @@ __device__ __forceinline__ int admission_status(const MetaArgs& a, const Admissi
 // counts and table lengths of the first kAdmitStage requests are staged in LDS, all of their
 // loads in flight at once.
 // ------------------------------------------------------------------------------------------
+template <bool kFreeChecked>
 __global__ __launch_bounds__(kPlanThreads) void admit_kernel(MetaArgs a) {
   __shared__ int lds[kPlanThreads / 64][4];
   __shared__ int first_error_req;
@@ -278,10 +286,10 @@ __global__ __launch_bounds__(kPlanThreads) void admit_kernel(MetaArgs a) {
   const int R = a.num_reqs;
   const int staged = min(R, kAdmitStage);
   int bad = INT_MAX;   // what count_kernel found in the free list (a thread's own requests)
-  if (!a.inplace) {
+  if constexpr (kFreeChecked) {
     for (int i = tid; i < R; i += kPlanThreads) bad = min(bad, a.admitted[i]);
+    if (tid == 0) first_bad = INT_MAX;
   }
-  if (tid == 0) first_bad = INT_MAX;
   int c[kAdmitStage / kPlanThreads], m[kAdmitStage / kPlanThreads];
 #pragma unroll
   for (int q = 0; q < kAdmitStage / kPlanThreads; ++q) {
@@ -297,8 +305,10 @@ __global__ __launch_bounds__(kPlanThreads) void admit_kernel(MetaArgs a) {
       blocks_s[i] = m[q];
     }
   }
-  __syncthreads();   // first_bad cleared
-  if (bad != INT_MAX) atomicMin(&first_bad, bad);
+  if constexpr (kFreeChecked) {
+    __syncthreads();   // first_bad cleared
+    if (bad != INT_MAX) atomicMin(&first_bad, bad);
+  }
   // (the admission's first barrier orders these LDS writes before every read)
   const Admission adm = admit_requests(
       a, [&](int i) { return i < kAdmitStage ? count_s[i] : a.live_count[i]; },
@@ -313,7 +323,7 @@ __global__ __launch_bounds__(kPlanThreads) void admit_kernel(MetaArgs a) {
       },
       lds, &first_error_req);
   admission_status(a, adm, adm.first_error == INT_MAX ? 0 : a.live_count[adm.first_error], true,
-                   nullptr, 0, &first_bad);
+                   nullptr, 0, kFreeChecked ? &first_bad : nullptr);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -807,8 +817,9 @@ hipError_t launch_build(const MetaArgs& a, hipStream_t stream) {
   const bool long_reqs = a.num_reqs > 0 && a.num_tokens / a.num_reqs >= kLongRequestTokens;
   const bool admit =
       a.num_reqs > kFusedAdmitReqs || (a.num_reqs > kFusedAdmitShortReqs && !long_reqs);
+  const bool check = admit && !a.inplace && a.free_len >= kCheckFreeEntries &&
+                     a.num_bt_entries >= kCheckFreeEntries;
   if (a.num_reqs > 0) {
-    const bool check = admit && !a.inplace;
     const auto count = long_reqs ? (check ? count_kernel<kCountThreads, true>
                                           : count_kernel<kCountThreads, false>)
                                  : (check ? count_kernel<kCountThreadsShort, true>
@@ -817,7 +828,8 @@ hipError_t launch_build(const MetaArgs& a, hipStream_t stream) {
                        dim3(long_reqs ? kCountThreads : kCountThreadsShort), 0, stream, a);
   }
   if (admit) {
-    hipLaunchKernelGGL(admit_kernel, dim3(1), dim3(kPlanThreads), 0, stream, a);
+    hipLaunchKernelGGL(check ? admit_kernel<true> : admit_kernel<false>, dim3(1),
+                       dim3(kPlanThreads), 0, stream, a);
     const auto plan = pow2 ? plan_kernel<true, true, kPlanThreadsSplit>
                            : plan_kernel<false, true, kPlanThreadsSplit>;
     hipLaunchKernelGGL(plan, dim3(a.num_reqs), dim3(kPlanThreadsSplit), 0, stream, a);

@@ -147,8 +147,7 @@ def test_append_by_number_of_new_slots(R, total, spread):
 @pytest.mark.parametrize("R", [256, 257, 600])
 @pytest.mark.parametrize("bad", [-1, 0, 1])
 def test_free_list_entry_outside_the_pool(R, bad):
-    """A bad entry before, at and after the last consumed one; batches whose admission is a
-    launch of its own (more than 256 short requests) look the list over beforehand."""
+    """A bad entry before, at and after the last consumed one."""
     t, B = torch(), _B()
     masks = [[1, 0] * 12] * R                       # 24 tokens, 3 blocks, 12 live: 2 blocks
     used = 2 * R
@@ -161,6 +160,32 @@ def test_free_list_entry_outside_the_pool(R, bad):
     t.cuda.synchronize()
     c = plan.counters.cpu().tolist()
     if bad <= 0:
+        assert c[3] == B.STATUS_CODE["VTOKEN_ERR_BLOCK_RANGE"] and c[0] == 0
+    else:
+        assert c[3] == 0 and c[0] == used
+
+
+@pytest.mark.parametrize("blocks", [54, 55])
+@pytest.mark.parametrize("bad", [0, 53, 54, 55, -1, 0.5, "after", "past"])
+def test_free_list_checked_by_the_count(blocks, bad):
+    """Large batches look over the usable entries of the free list, from 32,768 on, a share in each
+    workgroup of the count (600 requests of 54 blocks: 32,400, left to the admission; of 55: 33,000,
+    55 a workgroup): a bad entry at the ends of a share, among the last consumed, after them, and
+    past what a pass can use."""
+    t, B = torch(), _B()
+    R, S = 600, 8
+    masks = [([1, 0] * (S // 2)) * blocks] * R
+    used = R * -(-blocks // 2)
+    at = {"after": used, "past": R * blocks, -1: used - 1, 0.5: used // 2}.get(bad, bad)
+
+    def free(inp):
+        f = np.arange(R * blocks + 40, dtype=np.int32) % inp.num_blocks
+        f[at] = inp.num_blocks
+        return f
+    _, _, plan = _planned(masks, free=free)
+    t.cuda.synchronize()
+    c = plan.counters.cpu().tolist()
+    if at < used:
         assert c[3] == B.STATUS_CODE["VTOKEN_ERR_BLOCK_RANGE"] and c[0] == 0
     else:
         assert c[3] == 0 and c[0] == used

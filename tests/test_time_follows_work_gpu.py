@@ -128,3 +128,27 @@ def test_partial_planning_of_a_long_request_among_short_ones():
     alone, among = _plan_partial([600000]), _plan_partial([600000] + [100] * 511)
     print(f"[gpu] plan_partial 1 x 600K: {alone:.0f} us, among 511 x 100: {among:.0f} us", flush=True)
     assert among < 2.5 * alone
+
+
+def _build(R, tokens, free_blocks, S=16):
+    """us of the table build of R requests of `tokens` tokens, half live."""
+    t, B = torch(), _B()
+    rng = np.random.default_rng(R)
+    M = R * -(-tokens // S)
+    perm = rng.permutation(M + free_blocks)
+    kv = t.zeros((2, perm.size, S, 1, 8), dtype=t.float16, device="cuda")
+    live = t.from_numpy((rng.random(R * tokens) < 0.5).astype(np.uint8)).cuda()
+    batch = B.Batch(_i32(np.full(R, tokens)), _i32(np.arange(R + 1) * tokens),
+                    _i32(np.arange(R + 1) * (M // R)), _i32(perm[:M]), live, _i32(perm[M:]))
+    cache, plan = B.KVCache(kv, 1, 1, 8, S), B.Plan.allocate(batch, S)
+    us = _us(lambda: B.build_token_table(cache, batch, plan))
+    assert int(plan.counters[3]) == 0
+    return us
+
+
+def test_build_with_a_long_free_list():
+    """A pass can use no more of the free list than the batch has table entries: three million free
+    blocks cost small requests nothing (looked over to the end, twice the time)."""
+    few, many = _build(257, 20, 3000), _build(257, 20, 3000000)
+    print(f"[gpu] build, 3K blocks free: {few:.1f} us, 3M: {many:.1f} us", flush=True)
+    assert many < 1.5 * few
