@@ -2,7 +2,7 @@
 // decode attention that reads the (repacked) KV cache through it.
 //
 //   slot_indptr_kernel   exclusive scan of the live counts (one workgroup; batches of more than
-//                        4,096 requests)
+//                        2,048 requests)
 //   slot_map_kernel      one workgroup per request: wave-ballot compaction of token_slot,
 //                        the live tokens' slots in logical order (Sec. 3.4: the slot mapping
 //                        is built through the token table, once per token)
@@ -71,11 +71,12 @@ __global__ __launch_bounds__(1024) void slot_indptr_kernel(SlotMapArgs a) {
 // One workgroup per request compacts its live token slots in logical order: tiles of
 // 16 waves x kSlotBallots x 64 tokens, every token_slot load of a tile in flight before its
 // ballots, one pair of barriers per tile. kOffsets: each workgroup sums the counts of the
-// requests before its own itself (at most kSlotOffsetReqs, four loads per thread, in flight with
-// the first tile) and no launch of slot_indptr_kernel goes before (plan and mapping of 27 requests
-// of 200 tokens 20.7 -> 18.0 us; the first of a decode step's calls).
+// requests before its own itself (at most kSlotOffsetReqs, two loads per thread, in flight with
+// the first tile) and no launch of slot_indptr_kernel goes before: mapping of 8 requests of 300
+// tokens 5.9 -> 4.0 us, 1,024 of 5,000 11.0 -> 9.3, 2,048 of 100 15.2 -> 13.9; at 4,096 requests the
+// sums cost more than the launch (of 50 tokens 26.2 and 26.8 us, of 1,000 27.2 and 28.2).
 constexpr int kSlotBallots = 8;
-constexpr int kSlotOffsetReqs = 4096;
+constexpr int kSlotOffsetReqs = 2048;
 
 template <bool kOffsets>
 __global__ __launch_bounds__(1024) void slot_map_kernel(SlotMapArgs a) {

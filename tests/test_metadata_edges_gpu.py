@@ -30,10 +30,10 @@ def _planned(masks, S=8, free=None, inplace=False):
     return inp, batch, plan
 
 
-@pytest.mark.parametrize("R", [1, 63, 1024, 1025, 4096, 4097])
+@pytest.mark.parametrize("R", [1, 63, 1024, 1025, 2048, 2049, 4096, 4097])
 @pytest.mark.parametrize("reserve", [0, 3])
 def test_slot_mapping_offsets(R, reserve):
-    """4,096 requests is the last batch whose workgroups sum the counts before theirs."""
+    """2,048 requests is the last batch whose workgroups sum the counts before theirs."""
     t, B = torch(), _B()
     rng = np.random.default_rng(R)
     masks = [list((rng.random(int(n)) < 0.6).astype(int)) for n in rng.integers(1, 12, R)]
