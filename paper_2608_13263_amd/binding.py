@@ -410,9 +410,11 @@ def check_layout(cache: KVCache, batch: Batch, workspace=None, stream=None):
 def run_pass(cache: KVCache, batch: Batch, plan: Optional[Plan] = None, stream=None,
              inplace: bool = False) -> Plan:
     """One repack pass enqueued in order on one stream: the table build, then the copy and the
-    freed list in one launch (vtoken_repack_free, vtoken_repack_inplace_free)."""
+    freed list in one launch (vtoken_repack_free, vtoken_repack_inplace_free). A small pass is
+    bound by these calls' host side, so the stream is looked up once."""
     if plan is None:
         plan = Plan.allocate(batch, cache.block_size, device=cache.kv.device, inplace=inplace)
+    stream = _stream(stream)
     if inplace:
         build_token_table_inplace(cache, batch, plan, stream)
         repack_inplace_free(cache, batch, plan, stream=stream)
@@ -624,6 +626,7 @@ def run_partial_pass(cache: KVCache, batch: Batch, slot_in, plan: Optional[Plan]
     if state is None:
         state = PlannerState.allocate(cache.num_blocks, batch, device=cache.kv.device,
                                       pinned=pinned)
+    stream = _stream(stream)
     plan_partial(cache, batch, slot_in, plan, state, params, stream)
     repack(cache, batch, plan, stream)
     return plan, state

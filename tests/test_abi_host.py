@@ -449,3 +449,34 @@ def test_binding_reuses_structs_until_an_attribute_changes():
     p1 = plan.c()
     plan.counters = t(5)
     assert plan.c() is not p1 and plan.c().counters == plan.counters.data_ptr()
+
+
+@pytest.mark.parametrize("call", ["out_of_place", "in_place", "partial"])
+def test_pass_looks_its_stream_up_once(monkeypatch, call):
+    """A pass of two calls asks torch for the current stream once, and both calls get it."""
+    import types
+
+    import torch
+    asked, got = [], []
+
+    class Library:
+        def __getattr__(self, name):
+            return lambda *args: got.append((name, args[-1])) or 0
+
+    def current_stream():
+        asked.append(1)
+        return types.SimpleNamespace(cuda_stream=0x1230 + len(asked))
+    monkeypatch.setattr(B, "load_library", lambda: Library())
+    monkeypatch.setattr(torch.cuda, "current_stream", current_stream)
+    cache, batch, plan = (types.SimpleNamespace(c=lambda s=s: s, freed=torch.zeros(4))
+                          for s in (B.CCache(), B.CBatch(), B.CPlan()))
+    if call == "partial":
+        state = types.SimpleNamespace(c=lambda: B.CPlannerState())
+        B.run_partial_pass(cache, batch, torch.zeros(4), plan, state)
+    else:
+        B.run_pass(cache, batch, plan, inplace=call == "in_place")
+    assert len(asked) == 1
+    assert [s for _, s in got] == [0x1231] * 2, got
+    if call == "out_of_place":   # a stream that is given is not looked up
+        B.run_pass(cache, batch, plan, stream=77)
+        assert len(asked) == 1 and [s for _, s in got[2:]] == [77] * 2
