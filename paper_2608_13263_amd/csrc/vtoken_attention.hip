@@ -264,6 +264,10 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+// the same in the caller's outputs and workspace, which are aligned to a float and no more
+typedef f32x4 f32x4_out __attribute__((aligned(4)));
+typedef f32x2 f32x2_in __attribute__((aligned(4)));
 
 // The matrix-core operand type of the scores: fp16 caches multiply in fp16, bf16 and fp8
 // caches in bf16 (every e4m3 value is exact in bf16).
@@ -814,7 +818,7 @@ void decode_split_kernel(AttnArgs a) {
       L += wr[1] * f;
     }
     if (a.splits == 1) {
-      *reinterpret_cast<f32x4*>(a.out + (qh0 + g) * kD + d) = v * (1.f / L);
+      *reinterpret_cast<f32x4_out*>(a.out + (qh0 + g) * kD + d) = v * (1.f / L);
       continue;
     }
     float* rec = a.workspace + ((qh0 + g) * a.splits + split) * (kD + 2);
@@ -844,7 +848,7 @@ constexpr int kCombineManySplits = 32;   // more splits: 16 waves
 template <int kWaves, bool kShorten>
 __global__ __launch_bounds__(64 * kWaves) void decode_combine_kernel(AttnArgs a) {
   constexpr int kMaxD = 256;
-  __shared__ float sum_s[kWaves][kMaxD];
+  __shared__ __attribute__((aligned(8))) float sum_s[kWaves][kMaxD];
   const int qh = blockIdx.x % a.num_q_heads;
   const int r = blockIdx.x / a.num_q_heads;
   if (r >= a.num_reqs) return;
@@ -865,11 +869,10 @@ __global__ __launch_bounds__(64 * kWaves) void decode_combine_kernel(AttnArgs a)
     return;
   }
   const float* rec0 = a.workspace + ((int64_t)r * a.num_q_heads + qh) * a.splits * rs;
-  // A record's values: float pairs (its start and its stride are even), pair lane and lane + 64
+  // A record's values in float pairs: pair lane and lane + 64
   const int p0 = lane * 2, p1 = 128 + lane * 2;
-  typedef float f32x2 __attribute__((ext_vector_type(2)));
   auto pair = [&](int s, int p) {
-    return s < ns && p < D ? *reinterpret_cast<const f32x2*>(rec0 + s * rs + 2 + p)
+    return s < ns && p < D ? *reinterpret_cast<const f32x2_in*>(rec0 + s * rs + 2 + p)
                            : f32x2{0.f, 0.f};
   };
   f32x2 x0[kCombinePre], x1[kCombinePre];
@@ -879,7 +882,7 @@ __global__ __launch_bounds__(64 * kWaves) void decode_combine_kernel(AttnArgs a)
     x1[j] = pair(wave + j * kWaves, p1);
   }
   auto head_of = [&](int s) {   // (m_s, l_s)
-    return s < ns ? *reinterpret_cast<const f32x2*>(rec0 + s * rs) : f32x2{-INFINITY, 0.f};
+    return s < ns ? *reinterpret_cast<const f32x2_in*>(rec0 + s * rs) : f32x2{-INFINITY, 0.f};
   };
   const f32x2 first = head_of(lane);
   float M = first.x;

@@ -80,3 +80,28 @@ def test_decode_bound_in_the_middle_of_two_units():
     assert torch.allclose(out[0], full[0], rtol=1e-4, atol=1e-5)
     assert torch.isnan(out[1]).all() and not torch.isnan(full[1]).any()
     assert (out[2] == 0).all()
+
+
+@pytest.mark.parametrize("D", [32, 128, 256])
+@pytest.mark.parametrize("counts,bound", [([20, 1, 60], 60), ([700, 33, 5000], 5000)])
+def test_decode_into_unaligned_buffers(D, counts, bound):
+    """q, out and the workspace are aligned to a float: written by the split kernel (one split) and
+    by the merge, the same values as in aligned buffers and nothing beside them."""
+    g = torch.Generator().manual_seed(D)
+    total = sum(counts)
+    cache = B.KVCache(torch.randn(2, total, 1, 2, D, generator=g).bfloat16().cuda(), 1, 2, D, 1)
+    q = torch.randn(len(counts), 8, D, generator=g).cuda()
+    indptr = torch.tensor(np.concatenate([[0], np.cumsum(counts)]), dtype=torch.int32).cuda()
+    slots = torch.randperm(total, generator=g).to(torch.int32).cuda()
+    want = B.paged_decode(cache, q, indptr, slots, 0, bound)
+    need = B.decode_workspace_bytes(len(counts), 8, D, bound) // 4
+    for off in (1, 2, 3):
+        def shifted(n, fill):
+            return torch.full((n + 8,), fill, device="cuda")
+        buf, ws, qs = shifted(q.numel(), 7.0), shifted(need, 7.0), shifted(q.numel(), 0.0)
+        qs[off:off + q.numel()] = q.flatten()
+        B.paged_decode(cache, qs[off:off + q.numel()].view(q.shape), indptr, slots, 0, bound,
+                       out=buf[off:off + q.numel()].view(q.shape), workspace=ws[off:off + need])
+        assert torch.equal(buf[off:off + q.numel()].view(q.shape), want)
+        assert (buf[:off] == 7).all() and (buf[off + q.numel():] == 7).all()
+        assert (ws[:off] == 7).all() and (ws[off + need:] == 7).all()
