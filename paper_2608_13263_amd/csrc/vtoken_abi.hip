@@ -181,7 +181,9 @@ vtoken_status repack_in_place(const vtoken_cache* cache, const vtoken_batch* bat
     a.freed = freed;
     a.freed_capacity = freed_capacity;
   }
-  return hip_status(vtoken::launch_repack_inplace(a, variant, stream));
+  const int64_t held = batch->num_bt_entries * cache->block_size * row * a.num_planes;
+  return hip_status(
+      vtoken::launch_repack_inplace(a, variant, batch->num_tokens, held, stream));
 }
 }  // namespace
 

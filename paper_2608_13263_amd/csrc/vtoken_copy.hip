@@ -512,25 +512,26 @@ constexpr int vmcnt_imm(int n) {
 //
 // Bound: HBM where there are thousands of chains, else what one compute unit gets out of rows
 // far apart (16 KiB in flight per wave instead of 8 change nothing, the same waves on four times
-// the compute units nearly double the rate). So a launch of fewer than kInplaceFewChains
-// chains has workgroups of one wave (kFew). Whole passes, before (one workgroup per (request,
+// the compute units nearly double the rate). So a launch of few chains (launch_inplace_rows) has
+// workgroups of one wave (kFew). Whole passes, before (one workgroup per (request,
 // plane), a block at a time) and with workgroups of four waves and of one: fp8, 13 requests of
 // 100K tokens, 1 layer x 8 heads x 128 (208 chains) 3,361, 1,631 and 951 us; bf16, 2 of 80K,
 // 4 layers x 2 x 64 (32) 657, 355, 219; bf16, 6 of 72K, 32 x 2 x 64 (768) 4,627, 2,060, 1,935;
 // Llama-3-8B, 4 of 2-8K (4,096) 368, 337, 394. Non-temporal stores gain where HBM bounds
 // (Llama-3-70B at TP 8, 16 of 16-64K, H2O: 977 us with plain stores, 929 so) and lose with few
-// chains (2 of 43K, 32 x 1 x 128, 256 chains: 158 us plain, 167 so).
+// chains (2 of 43K, 32 x 1 x 128, 256 chains: 158 us plain, 167 so) and in batches that the caches
+// hold a good part of (kPlain).
 constexpr int kLongestFirstMaxReqs = 256;
 constexpr int kInplaceGroup = 8;                          // instructions of a group
 
-template <int kV, int kWsh, bool kFew>
+template <int kV, int kWsh, int kMoveTile, bool kFew, bool kPlain>
 __global__ __launch_bounds__(kFew ? 64 : kCopyThreads)
 __attribute__((amdgpu_waves_per_eu(kFew ? 2 : 4)))
 void repack_inplace_rows_kernel(InplaceArgs a, int slices, int64_t items) {
   constexpr int kThreads = kFew ? 64 : kCopyThreads;
   constexpr int kWaves = kThreads / 64;
-  constexpr int kMoveTile = kFew ? 16 : 8;             // rows a thread stages
-  constexpr int kMoveRows = kThreads * kMoveTile;      // destination rows staged at a time
+  constexpr int kMoveRows = kThreads * kMoveTile;      // destination rows staged at a time,
+                                                       // kMoveTile by a thread
   constexpr int kRows = 64 >> kWsh;                    // rows of an instruction
   constexpr int kGroup = kV * kRows;                   // rows of a group
   __shared__ int2 move_s[kMoveRows + 2 * kGroup];
@@ -663,7 +664,7 @@ void repack_inplace_rows_kernel(InplaceArgs a, int slices, int64_t items) {
     };
     auto put = [&](int slot, u32x4 val) {
       u32x4* p = reinterpret_cast<u32x4*>(base + (int64_t)slot * a.row_bytes);
-      if constexpr (kFew) {
+      if constexpr (kPlain) {
         *p = val;
       } else {
         __builtin_nontemporal_store(val, p);
@@ -731,27 +732,50 @@ void repack_inplace_rows_kernel(InplaceArgs a, int slices, int64_t items) {
 // down to 128-byte slices until the launch has kInplaceChains chains (bf16, 9 requests of
 // 5-23K, 32 layers x 8 x 128: 1,416 us with 4,608 chains, 1,398 with 18,432; bf16, 38 of 8K, 16
 // layers: 1,590 and 1,561). Rows that are no whole number of 128-byte lines lose more to lines
-// shared by slices: those are cut, down to 64 bytes, for kInplaceOddChains only (960-byte rows,
-// 168 pairs: 78 us in 168 chains, 46 in 672; 2 pairs: 778 us in 2, 253 in 30).
+// shared by slices: those are cut, down to 64 bytes, for kInplaceOddChains only, and a wave of
+// theirs takes groups of 16 instructions instead (pairs of a request and a plane; us, cut for 512
+// chains / for 160 / the copy before the row walk: 480-byte rows, 448 pairs of 5,000 tokens
+// 215 / 147 / 155, 160 of 800 18.1 / 11.1 / 11.8; 960-byte rows, 448 of 5,000 411 / 323 / 311, 168
+// of 5,000 124 / 132 / 143, 16 of 30,000 118 / 118 / 523, and 148 cut for 128 chains).
 constexpr int64_t kInplaceChains = 16384;
-constexpr int64_t kInplaceOddChains = 512;
+constexpr int64_t kInplaceOddChains = 160;
+// Launches of fewer chains have workgroups of one wave (above); with at most kInplaceNarrow slices
+// to a row, where the waves of a workgroup share little, up to kInplaceFewNarrow: bf16, 32 layers
+// x 2 x 64, 10 requests of 3,000 (1,280 chains) 73.9 us with workgroups of four, 55.4 so (55.6
+// before the row walk); fp8, 80 x 1 x 128, 8 of 4,000 (1,280) 113 and 81 (104). With 4 slices of a
+// row four waves are better (fp8, 32 x 4 x 128, 8 of 500, 2,048 chains: 26.3 and 29.2).
 constexpr int64_t kInplaceFewChains = 1024;
+constexpr int64_t kInplaceFewNarrow = 4096;
+constexpr int kInplaceNarrow = 2;
+// Plain stores, besides launches of fewer than kInplaceFewChains chains, where the caches hold a
+// good part of the batch's blocks: bf16, 32 x 8 x 128, 8 of 500 (262 MB) 98 us with non-temporal
+// ones, 80 so (78 before the row walk); 16 x 8 x 128, 4 of 4,000 (1.05 GB) 142 and 117 (169). Larger
+// batches (Llama-3-8B, 4 of 2-8K, 2.7 GB: 327 and 337; 70B at TP 8: 909 and 939), those of more
+// chains than kInplaceChains and the smallest (Llama-3-8B, 1 of 600: 17.0 and 17.4) keep
+// non-temporal ones.
+constexpr int64_t kInplacePlainMin = 96LL << 20;
+constexpr int64_t kInplacePlainMax = 1LL << 30;
+// One-wave workgroups stage 1,024 rows at a time, 512 where the requests average fewer tokens than
+// kInplaceShort (8 of 300, 1 layer x 2 x 64: 7.6 and 6.6 us; 2 of 30,000, 4 x 5 x 96: 118 and 124).
+constexpr int64_t kInplaceShort = 1024;
 constexpr int64_t kMaxInplaceGrid = 1 << 22;
 
-template <bool kFew>
+template <int kMoveTile, bool kFew, bool kPlain>
 auto inplace_rows_kernel(int wsh) -> void (*)(InplaceArgs, int, int64_t) {
+  constexpr int kOddGroup = kFew ? 2 * kInplaceGroup : kInplaceGroup;
   switch (wsh) {
-    case 0: return repack_inplace_rows_kernel<kInplaceGroup, 0, kFew>;
-    case 1: return repack_inplace_rows_kernel<kInplaceGroup, 1, kFew>;
-    case 2: return repack_inplace_rows_kernel<kInplaceGroup, 2, kFew>;
-    case 3: return repack_inplace_rows_kernel<kInplaceGroup, 3, kFew>;
-    case 4: return repack_inplace_rows_kernel<kInplaceGroup, 4, kFew>;
-    case 5: return repack_inplace_rows_kernel<kInplaceGroup, 5, kFew>;
-    default: return repack_inplace_rows_kernel<kInplaceGroup, 6, kFew>;
+    case 0: return repack_inplace_rows_kernel<kInplaceGroup, 0, kMoveTile, kFew, kPlain>;
+    case 1: return repack_inplace_rows_kernel<kInplaceGroup, 1, kMoveTile, kFew, kPlain>;
+    case 2: return repack_inplace_rows_kernel<kInplaceGroup, 2, kMoveTile, kFew, kPlain>;
+    case 3: return repack_inplace_rows_kernel<kInplaceGroup, 3, kMoveTile, kFew, kPlain>;
+    case 4: return repack_inplace_rows_kernel<kInplaceGroup, 4, kMoveTile, kFew, kPlain>;
+    case 5: return repack_inplace_rows_kernel<kOddGroup, 5, kMoveTile, kFew, kPlain>;
+    default: return repack_inplace_rows_kernel<kOddGroup, 6, kMoveTile, kFew, kPlain>;
   }
 }
 
-hipError_t launch_inplace_rows(const InplaceArgs& a, hipStream_t stream) {
+hipError_t launch_inplace_rows(const InplaceArgs& a, int64_t num_tokens, int64_t held_bytes,
+                               hipStream_t stream) {
   int wsh = 0;   // log2 units of a slice
   while (wsh < 6 && (1 << wsh) < a.row_units) ++wsh;
   const int64_t pairs = (int64_t)a.num_reqs * a.num_planes;
@@ -760,7 +784,9 @@ hipError_t launch_inplace_rows(const InplaceArgs& a, hipStream_t stream) {
   const int64_t most = lines ? kInplaceChains : kInplaceOddChains;
   while (wsh > (lines ? 3 : 2) && pairs * slices_of(wsh) < most) --wsh;
   const int slices = slices_of(wsh);
-  const bool few = pairs * slices < kInplaceFewChains;
+  const int64_t chains = pairs * slices;
+  const bool few = chains < (slices <= kInplaceNarrow ? kInplaceFewNarrow : kInplaceFewChains);
+  const bool small = held_bytes < kInplacePlainMax;
   const int threads = few ? 64 : kCopyThreads;
   const int waves = threads / 64;
   const int64_t items = a.num_reqs * (((int64_t)a.num_planes * slices + waves - 1) / waves);
@@ -768,7 +794,17 @@ hipError_t launch_inplace_rows(const InplaceArgs& a, hipStream_t stream) {
   const int64_t total = items + a.free_reqs;
   const int64_t gx = total < kMaxInplaceGrid ? total : kMaxInplaceGrid;
   const dim3 grid(static_cast<unsigned>(gx), static_cast<unsigned>((total + gx - 1) / gx));
-  const auto kernel = few ? inplace_rows_kernel<true>(wsh) : inplace_rows_kernel<false>(wsh);
+  void (*kernel)(InplaceArgs, int, int64_t) = nullptr;
+  if (few) {
+    const bool is_short = num_tokens < a.num_reqs * kInplaceShort;
+    kernel = chains >= kInplaceFewChains && !small ? inplace_rows_kernel<16, true, false>(wsh)
+             : is_short                            ? inplace_rows_kernel<8, true, true>(wsh)
+                                                   : inplace_rows_kernel<16, true, true>(wsh);
+  } else {
+    const bool plain = small && held_bytes >= kInplacePlainMin && chains < kInplaceChains;
+    kernel = plain ? inplace_rows_kernel<8, false, true>(wsh)
+                   : inplace_rows_kernel<8, false, false>(wsh);
+  }
   hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, stream, a, slices, items);
   return hipGetLastError();
 }
@@ -808,11 +844,14 @@ hipError_t launch_inplace_s(const InplaceArgs& a, int variant, hipStream_t strea
 
 }  // namespace
 
-hipError_t launch_repack_inplace(const InplaceArgs& a, int variant, hipStream_t stream) {
+hipError_t launch_repack_inplace(const InplaceArgs& a, int variant, int64_t num_tokens,
+                                 int64_t held_bytes, hipStream_t stream) {
   if (variant < 0 || variant > 4) return hipErrorInvalidValue;
   if ((int64_t)a.num_reqs * a.num_planes <= 0) return hipSuccess;
   if ((int64_t)a.chunk_units * 16 > kMaxInplaceChunkBytes) return hipErrorInvalidValue;
-  if (variant == 0 || variant == 4) return launch_inplace_rows(a, stream);
+  if (variant == 0 || variant == 4) {
+    return launch_inplace_rows(a, num_tokens, held_bytes, stream);
+  }
   return a.block_size <= 64 ? launch_inplace_s<true>(a, variant, stream)
                             : launch_inplace_s<false>(a, variant, stream);
 }

@@ -380,7 +380,9 @@ __host__ __device__ constexpr int64_t decode_grid_groups(int64_t n) { return (n 
 
 hipError_t launch_build(const MetaArgs& a, hipStream_t stream);
 // variant: 0 default (4), 1 LDS double buffer, 2 LDS single buffer, 3 registers, 4 row walk
-hipError_t launch_repack_inplace(const InplaceArgs& a, int variant, hipStream_t stream);
+// (num_tokens and held_bytes, the batch's tokens and the bytes of its blocks, only pick the kernel)
+hipError_t launch_repack_inplace(const InplaceArgs& a, int variant, int64_t num_tokens,
+                                 int64_t held_bytes, hipStream_t stream);
 hipError_t launch_free(const MetaArgs& a, int32_t* freed, int64_t freed_capacity,
                        hipStream_t stream);
 // The layout check (vtoken_layout.hip): words[0] is the flag word, words[1 ..] one bit per

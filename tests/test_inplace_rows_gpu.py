@@ -66,3 +66,49 @@ def test_freed_list_in_the_copy_launch(reqs):
         for k in want:
             assert np.array_equal(got[k], want[k]), k
         assert t.equal(kv.view(t.uint8), kv2.view(t.uint8))
+
+
+# (dtype, layers, heads, dim, S, requests, tokens): what each launch takes stands beside it
+LAUNCHES = [
+    ("bf16", 32, 2, 64, 48, 7, 3000),       # 896 chains: one wave a workgroup
+    ("bf16", 32, 2, 64, 48, 8, 3000),       # 1,024, two slices a row: still
+    ("bf16", 32, 2, 64, 48, 31, 900),       # 3,968, short requests
+    ("bf16", 32, 2, 64, 48, 32, 1000),      # 4,096: four waves, plain stores (524 MB)
+    ("bf16", 32, 2, 64, 48, 10, 7000),      # 1,280 chains of 1.1 GB: one wave, non-temporal
+    ("fp8", 16, 8, 128, 16, 8, 2000),       # 2,048 chains, eight slices: four waves, plain
+    ("fp8", 32, 4, 128, 16, 8, 300),        # below 96 MiB: non-temporal
+    ("bf16", 32, 8, 128, 16, 4, 2100),      # 1.1 GB: non-temporal
+    ("bf16", 32, 8, 128, 16, 20, 300),      # 20,480 chains: non-temporal
+    ("bf16", 12, 5, 96, 16, 6, 800),        # 144 pairs of 960-byte rows: two slices
+    ("bf16", 20, 5, 96, 16, 4, 900),        # 160: one, groups of 16, short requests
+    ("bf16", 20, 5, 96, 24, 4, 5000),       # long ones
+    ("fp8", 32, 5, 96, 8, 1, 2500),         # 64 pairs of 480-byte rows: four slices
+    ("fp8", 32, 5, 96, 16, 7, 3000),        # 448: one
+    ("fp8", 80, 5, 96, 16, 30, 400),        # 4,800: four waves, plain
+    ("bf16", 1, 3, 8, 16, 9, 2000),         # 48-byte rows
+]
+
+
+@pytest.mark.parametrize("dtype,layers,heads,dim,S,reqs,tokens", LAUNCHES)
+def test_every_launch_of_the_row_walk(dtype, layers, heads, dim, S, reqs, tokens):
+    """Workgroups of one wave and of four, both kinds of stores, both lengths of the staged list and
+    of a group, against the block-staging copy (variant 3) on the same cache: every byte."""
+    t = torch()
+    from paper_2608_13263_amd import binding as B
+    rng = np.random.default_rng(layers * reqs)
+    lens = rng.integers(tokens * 3 // 4, tokens * 5 // 4, reqs)
+    masks = [(rng.random(int(n)) < 0.4).astype(np.uint8) for n in lens]
+    shape = W.KVShape(layers, heads, dim, S, {"fp8": "fp8_e4m3"}.get(dtype, dtype))
+    inp = W.from_masks(masks, shape, free_blocks=2, seed=reqs)
+    kv = t.randint(0, 256, (2 * layers, inp.num_blocks, S, shape.row_bytes), dtype=t.uint8,
+                   device="cuda")
+    typed = [x.view(t.uint8 if dtype == "fp8" else t.bfloat16)
+             .view(2 * layers, inp.num_blocks, S, heads, dim) for x in (kv, kv.clone())]
+    batch = B.Batch.from_inputs(inp)
+    for x, variant in zip(typed, (0, 3)):
+        cache = B.KVCache(x, layers, heads, dim, S)
+        plan = B.Plan.allocate(batch, S, inplace=True)
+        B.build_token_table_inplace(cache, batch, plan)
+        B.repack_inplace_ex(cache, batch, plan, variant=variant)
+        assert int(plan.counters[3]) == 0 and int(plan.counters[1]) > 0
+    assert t.equal(typed[0].view(t.uint8), typed[1].view(t.uint8))
