@@ -1393,7 +1393,7 @@ def run_overlap(args, inp, kv, cache, batch, plan, stream):
                 cop.append(ev[0].elapsed_time(ev[1]))
                 both.append(max(ev[0].elapsed_time(ev[1]), ev[0].elapsed_time(ev[3])))
         mean = lambda x: sum(x) / len(x)  # noqa: E731
-        return {"grid_cap": cap or 1 << 19, "copy_alone_ms": round(mean(alone), 4),
+        return {"grid_cap": cap or "default", "copy_alone_ms": round(mean(alone), 4),
                 "decode_alone_ms": round(decode_ms, 4),
                 "decode_with_copy_ms": round(mean(dec), 4),
                 "copy_with_decode_ms": round(mean(cop), 4),

@@ -29,7 +29,7 @@ def test_traffic_records_resolve_only_on_their_source():
     """A record whose kernel source still hashes as recorded is returned; one taken on an
     earlier source is ignored (the bench then reports null traffic)."""
     recs = _records()
-    assert {r[0] for r in recs} >= {"repack_direct_kernel", "repack_inplace_pipe_kernel",
+    assert {r[0] for r in recs} >= {"repack_direct_kernel", "repack_inplace_rows_kernel",
                                     "vtoken_paged_decode"}
     for kernel, workload, src, sha, alg, traffic in recs:
         assert 0.99 < int(traffic) / int(alg) < 1.2
