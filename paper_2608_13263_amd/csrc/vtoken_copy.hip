@@ -42,12 +42,13 @@ __device__ __forceinline__ int lanes_below(uint64_t mask) {
 //
 // Bound: HBM, where a piece's loads are in flight early enough. A piece is a chain of dependent
 // reads (counters, then destination block and plan entries, then rows) and then its stores, so
-// a workgroup that takes one small piece and ends is bound by that chain: 434K pieces of 4 KiB
-// (fp8, 80 layers, 2 heads x 64, S = 32) took 1.53 ms that way, 2.3 TB/s. Every workgroup
+// a workgroup that takes one small piece and ends is bound by that chain: 404K pieces of 4 KiB
+// (fp8, 80 layers, 2 heads x 64, S = 32) took 1.48 ms that way, 2.2 TB/s. Every workgroup
 // therefore walks pieces with two of them in flight: the next piece's loads are issued before
-// this one's stores, and the plan entries of the one after that before either (that call: 0.59
-// ms, 5.9 TB/s; 2 KiB chunks, S = 8: 2.20 -> 1.72 ms; 8 KiB chunks: 478 -> 375 us; 32 KiB pieces
-// are at the rate of a plain copy either way).
+// this one's stores, and the plan entries of the one after that before either (that call: 0.67
+// ms, 4.9 TB/s; 1,600K pieces of 2 KiB, bf16, S = 8: 1.63 -> 1.31 ms; 205K of 8 KiB, fp8, S = 64:
+// 766 -> 678 us; 32 KiB pieces are at the rate of a plain copy, up to 0.7% slower for the registers
+// that the walk takes).
 //
 // Source slots of one destination block: with S <= 64, lane j of every wave holds
 // src_plan[g*S + j] and rows are picked with a cross-lane shuffle; otherwise each unit reads
